@@ -242,8 +242,8 @@ static int32_t make_tilek(const ss_tile* t, const ss_sun* s, const Resolved& rp,
   K->RW = whole ? W : t->ray_w;
   K->RH = whole ? H : t->ray_h;
   for (int m = 0; m < L; ++m) {
-    dims_of(W, H, m, &K->lw[m], &K->lh[m]);
-    K->loff[m] = m == 0 ? 0 : (int)ss_maxmip_level_offset(W, H, m);
+    dims_of(W, H, m, &K->lev[m].w, &K->lev[m].h);
+    K->lev[m].p = m == 0 ? t->height : t->maxmip + ss_maxmip_level_offset(W, H, m);
   }
   const double e = s->elev_rad, a = s->azim_rad;
   const double ce = cos(e);
@@ -280,16 +280,18 @@ static int32_t make_tilek(const ss_tile* t, const ss_sun* s, const Resolved& rp,
     if (rp.schedule == SS_SCHED_LIST) np = rp.n_prime_list[j];
     if (np > L) np = L;
     if (np < 1) np = 1;
-    K->m0[j] = np - 1;
-    K->a0[j] = ga;
+    K->run[j] = run_pack(ga, np - 1);
     K->tau[j] = run_start_len(ga, half_delta);
-    ga += 2 << K->m0[j];
+    ga += 2 << (np - 1);
     covered += ldexp(1.0, np - 1);
     j++;
     if (rp.n_segments > 0 ? j >= rp.n_segments : covered >= need) break;
   }
   K->nseg = j;
   K->tau[j] = run_start_len(ga, half_delta);
+  for (int k = 0; k < SS_FITRUNS; ++k)
+    K->fit_err[k] = k < j ? run_fit_err(W, H, K->texel, K->invR, K->Lz, half_delta, K->run[k])
+                          : SS_FIT_NONE;
   const double tau = (double)(ga + 1) * half_delta;
   // uniform steps stop at the cap, or without one at the tile edge and at the
   // latest after the runs' extent (the tile diagonal)

@@ -60,20 +60,12 @@ __device__ __forceinline__ int resolve_claim(const long long* __restrict__ item_
   return -1;
 }
 
-// Occupancy: the stepping modes are held to 8 wavefronts per SIMD (at most 64
-// VGPRs; the compiler spills a dword or two, outside the per-run loops), 5%
-// faster on the 4096^2 x 8-sun workload than the 7 their free allocation
-// gives; the exact mode to 7 (72 VGPRs, no spill), 6% faster than its free 6
-// and than 8 (which spills inside the walk).
 template <bool SPHERE, int TW, int MODE>
-__global__ __attribute__((amdgpu_flat_work_group_size(256, 256),
-                          amdgpu_waves_per_eu(MODE == SS_MODE_EXACT ? 7 : 8))) void batched_kernel(const TileK* __restrict__ pairs,
-                                                      float* const* __restrict__ outs,
-                                                      const long long* __restrict__ item_start,
-                                                      const long long* __restrict__ xstart,
-                                                      const int* __restrict__ pair_nbx,
-                                                      unsigned int* __restrict__ counter,
-                                                      int n_pairs) {
+SS_RAY_KERNEL void batched_kernel(const TileK* __restrict__ pairs, float* const* __restrict__ outs,
+                                  const long long* __restrict__ item_start,
+                                  const long long* __restrict__ xstart,
+                                  const int* __restrict__ pair_nbx,
+                                  unsigned int* __restrict__ counter, int n_pairs) {
   constexpr int TH = 64 / TW;
   // two slots: the item being worked and the next one; the next claim's index
   // and the queue search state live here too, so nothing extra stays in
@@ -148,7 +140,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(256, 256),
 static_assert(SS_ITEM_BLOCKS == 1, "the flat form reads the item prefix sums as block prefix sums");
 
 template <bool SPHERE, int TW, int MODE>
-__global__ __launch_bounds__(256) void flat_kernel(const TileK* __restrict__ pairs,
+SS_RAY_KERNEL void flat_kernel(const TileK* __restrict__ pairs,
                                                    float* const* __restrict__ outs,
                                                    const long long* __restrict__ block_start,
                                                    const int* __restrict__ pair_nbx, int n_pairs,
@@ -263,8 +255,9 @@ hipError_t launch_stage(void* d_dst, const void* h_src, size_t bytes, hipStream_
 }
 
 // One wavefront per pair: the TileK words come from the tile's template except
-// the sun fields (from the pair's record) and the run starts (formed from the
-// template's grid indices and the pair's delta/2, as the host set-up forms them).
+// the sun fields (from the pair's record), the run starts and the fits' error
+// bounds (formed from the template's runs and the pair's sun and delta/2, as the
+// host set-up forms them).
 static_assert(offsetof(TileK, ucap) == offsetof(TileK, Lx) + 11 * sizeof(float),
               "the sun fields of TileK are contiguous");
 static_assert(sizeof(TileK) % 4 == 0, "TileK is copied by words");
@@ -280,6 +273,7 @@ __global__ __launch_bounds__(64) void expand_kernel(const TileK* __restrict__ tm
   constexpr int NW = (int)(sizeof(TileK) / 4);
   constexpr int W_SUN = (int)(offsetof(TileK, Lx) / 4);
   constexpr int W_TAU = (int)(offsetof(TileK, tau) / 4);
+  constexpr int W_ERR = (int)(offsetof(TileK, fit_err) / 4);
   const int p = blockIdx.x;
   const int t = p / n_suns, k = p % n_suns;
   const int n_pairs = n_tiles * n_suns;
@@ -294,8 +288,11 @@ __global__ __launch_bounds__(64) void expand_kernel(const TileK* __restrict__ tm
       v = __float_as_uint(P.sun[w - W_SUN]);
     } else if (w >= W_TAU && w <= W_TAU + nseg) {
       const int j = w - W_TAU;
-      const int a = j < nseg ? T.a0[j] : T.a0[nseg - 1] + (2 << T.m0[nseg - 1]);
+      const int a = j < nseg ? run_a0(T.run[j])
+                             : run_a0(T.run[nseg - 1]) + (2 << run_m0(T.run[nseg - 1]));
       v = __float_as_uint(run_start_len(a, P.half_delta));
+    } else if (w >= W_ERR && w < W_ERR + SS_FITRUNS && w - W_ERR < nseg) {
+      v = run_fit_err(T.W, T.H, T.texel, T.invR, P.sun[2], P.half_delta, T.run[w - W_ERR]);
     }
     dst[w] = v;
   }

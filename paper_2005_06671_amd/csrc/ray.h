@@ -16,6 +16,13 @@
 
 #define SS_INF __builtin_inff()
 
+// Kernels that trace rays: 256 threads, held to 7 wavefronts per SIMD (72 VGPRs).
+// The descent is bound by instruction issue and gathers together, so wavefronts
+// in flight count: the 8 suns of a 4096^2 tile take 7.64 ms at the 6 its free
+// allocation (84) gives, 6.76 at 7 and 7.04 at 8, which spills in the levels.
+#define SS_RAY_KERNEL \
+  __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(7)))
+
 // Workgroup ids are dealt round-robin over the 8 XCDs.  xcd_remap gives each
 // XCD one contiguous run of [0, nb) (the first nb % 8 XCDs one id more);
 // xcd_remap_grouped does so inside each group of grp ids (grp a multiple of 8,
@@ -151,10 +158,6 @@ __device__ __forceinline__ float tip_rise_u(const Ray<SPHERE>& r, const TileK& T
   return u * T.Lz + r.dz;
 }
 
-__device__ __forceinline__ const float* level_ptr(const TileK& T, int m) {
-  return m == 0 ? T.h : T.mm + T.loff[m];
-}
-
 // Keeps an index inside [0, n): a negative index wraps to a huge unsigned
 // value and lands on n - 1.  Only rounding at a tile edge can produce an index
 // outside the level, so this is a memory-safety guard, not a behaviour.
@@ -168,8 +171,8 @@ __device__ __forceinline__ unsigned idx2(unsigned y, unsigned w, unsigned x) {
 }
 
 __device__ __forceinline__ float mip_at(const TileK& T, int m, int cx, int cy) {
-  const unsigned w = (unsigned)T.lw[m];
-  return level_ptr(T, m)[idx2(inside(cy, T.lh[m]), w, inside(cx, T.lw[m]))];
+  const LevelK k = T.lev[m];
+  return k.p[idx2(inside(cy, k.h), (unsigned)k.w, inside(cx, k.w))];
 }
 
 // One mip level as a buffer resource: 32-bit offsets, and an offset past the
@@ -177,22 +180,34 @@ __device__ __forceinline__ float mip_at(const TileK& T, int m, int cx, int cy) {
 // candidates that are then discarded need no clamping.
 struct Level {
   __amdgpu_buffer_rsrc_t rs;
-  int w;
+  int w, h;
 };
 
-__device__ __forceinline__ Level level_of(const TileK& T, int m) {
+__device__ __forceinline__ Level level_from(const LevelK& k) {
   Level L;
-  L.rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(level_ptr(T, m)), 0,
-                                           T.lw[m] * T.lh[m] * 4, 0x00020000);
-  L.w = T.lw[m];
+  L.rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(k.p), 0, k.w * k.h * 4, 0x00020000);
+  L.w = k.w;
+  L.h = k.h;
   return L;
 }
+
+__device__ __forceinline__ Level level_of(const TileK& T, int m) { return level_from(T.lev[m]); }
 
 // (A texel outside the level may give any offset; the range check makes the
 // load return 0 or an in-range value, and such candidates are discarded.)
 __device__ __forceinline__ float level_at(const Level& L, int cx, int cy) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
                                        L.rs, (int)(idx2((unsigned)cy, (unsigned)L.w, (unsigned)cx) * 4u), 0, 0));
+}
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// The value, and the two neighbours in a row, at a byte offset of a level.
+__device__ __forceinline__ float value_at(const Level& L, unsigned a) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(L.rs, (int)a, 0, 0));
+}
+__device__ __forceinline__ f32x2 pair_at(const Level& L, unsigned a) {
+  return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(L.rs, (int)a, 0, 0));
 }
 
 // Bilinear sample of the terrain below the ray tip at ray length t (u = u(t)):
@@ -287,33 +302,389 @@ __device__ __forceinline__ float tangent_key(float num, float den) {
   return den > 0.0f ? num * ss_rcp(den) : (num >= 0.0f ? SS_INF : -SS_INF);
 }
 
-// One concatenated run (Sec. 3.3): descent from level m0 = T.m0[j] over the
-// texels the ray crosses (Sec. 3.2, Fig. 3b), strict argmin from the far end
-// (kept here as '<=' scanning from the near end), then three samples half a
-// texel apart around the chosen base texel (Alg. 1, final level).
+// True when every sample at ray length >= t clears the angle whose tangent is
+// need_tan (an angle in (-pi/2, pi/2)), given that no terrain rises above
+// `top` (relative to the reference height hp, and at least the origin's dz,
+// i.e. not below the origin): the clearance of the point at that height below
+// the tip grows with t on the plane and on the sphere.  Used for the
+// result-invariant early exits.
 template <bool SPHERE>
-__device__ __forceinline__ void descend_run(const TileK& T, const Ray<SPHERE>& r, int jseg, SegOut& out,
-                                            unsigned& n_lb, unsigned& n_smp) {
-  out.valid = 0;
-  const float ta = T.tau[jseg], tb = T.tau[jseg + 1];
-  const float ua = t_to_u(r, ta);
-  const float ub = fminf(t_to_u(r, tb), r.uexit);
-  const int m = T.m0[jseg];
+__device__ __forceinline__ bool clears(const Ray<SPHERE>& r, const TileK& T, float t, float top,
+                                       float need_tan) {
+  const float d = tip_rise(r, T, t) - top;
+  if (!(d > 0.0f)) return false;
+  float num, den;
+  clearance_terms(r, t, d, num, den);
+  return den <= 0.0f || num >= need_tan * den;  // den <= 0: at least pi/2
+}
+
+// tan(min(alpha, r_L) + margin) for the tangent key of alpha (tan addition).
+__device__ __forceinline__ float need_tangent(const TileK& T, float key) {
+  const float k = fmaxf(fminf(key, T.tan_rL), -1e30f);
+  return (k + T.tan_margin) * ss_rcp(1.0f - k * T.tan_margin);
+}
+
+// The smallest of a run's final samples by height above the terrain (Alg. 1,
+// final level), as `<=` scanning from the near end.
+struct Deepest {
+  float dh, t, u;
+  int n;
+  bool found;
+};
+
+// The three samples n_c - 1, n_c, n_c + 1 of the half-texel grid
+// t_n = (n + 1) delta/2, any taps.
+template <bool SPHERE>
+__device__ __forceinline__ Deepest samples_any(const TileK& T, const Ray<SPHERE>& r, float ncf,
+                                               unsigned& n_smp) {
+  Deepest d{SS_INF, 0.0f, 0.0f, -1, false};
+  const int nc = (int)ncf;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int n = nc - 1 + k;
+    const float t = (float)(n + 1) * T.half_delta;
+    const float u = t_to_u(r, t);
+    if (n >= 0 && u < r.uexit) {
+      const Sample s = sample_at(r, T, t, u);
+      n_smp++;
+      if (s.dh <= d.dh) d = Deepest{s.dh, t, u, n, true};
+    }
+  }
+  return d;
+}
+
+// The same three samples where every tap lies inside the tile: no clamping, a
+// row's two taps with one 8-byte load, and all six loads issued before the
+// first is waited for (samples that do not count are evaluated and dropped;
+// the range check of the buffer keeps even their loads in bounds).
+template <bool SPHERE>
+__device__ __forceinline__ Deepest samples_inside(const TileK& T, const Ray<SPHERE>& r, float ncf,
+                                                  unsigned& n_smp) {
+  const Level L0 = level_of(T, 0);
+  const int base = __mul24(r.j, L0.w) + r.i;
+  float t[3], u[3], fx[3], fy[3];
+  f32x2 lo[3], hi[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    t[k] = (ncf + (float)k) * T.half_delta;
+    u[k] = t_to_u(r, t[k]);
+    const float dx = fmaf(r.Kx, u[k], r.ox), dy = fmaf(r.Ky, u[k], r.oy);
+    const float flx = floorf(dx), fly = floorf(dy);
+    fx[k] = dx - flx;
+    fy[k] = dy - fly;
+    const unsigned a = 4u * (unsigned)(__mul24((int)fly, L0.w) + ((int)flx + base));
+    lo[k] = pair_at(L0, a);
+    hi[k] = pair_at(L0, a + 4u * (unsigned)L0.w);
+  }
+  Deepest d{SS_INF, 0.0f, 0.0f, -1, false};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    // as sample_at
+    const float h00 = lo[k].x - r.hp, h10 = lo[k].y - r.hp;
+    const float h01 = hi[k].x - r.hp, h11 = hi[k].y - r.hp;
+    const float hb = (1.0f - fy[k]) * ((1.0f - fx[k]) * h00 + fx[k] * h10) +
+                     fy[k] * ((1.0f - fx[k]) * h01 + fx[k] * h11);
+    const float dh = tip_rise(r, T, t[k]) - hb;
+    const bool ok = ncf + (float)k >= 1.0f && u[k] < r.uexit;
+    n_smp += ok ? 1u : 0u;
+    const bool take = ok && dh <= d.dh;
+    d.dh = take ? dh : d.dh;
+    d.t = take ? t[k] : d.t;
+    d.u = take ? u[k] : d.u;
+    d.n = take ? (int)ncf - 1 + k : d.n;
+    d.found = d.found || take;
+  }
+  return d;
+}
+
+// Lane masks: a condition over the wavefront as a scalar, combined by scalar
+// instructions and turned back where a lane selects by it.
+typedef unsigned long long Lanes;
+__device__ __forceinline__ Lanes lanes(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool of(Lanes m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// 2 v + the lane's bit of m: one add with carry (two wait states after a mask the
+// vector unit may have written).
+__device__ __forceinline__ int twice_plus(int v, Lanes m) {
+  int out;
+  Lanes carry;
+  asm("s_nop 1\n\tv_addc_co_u32_e64 %0, %1, %2, %2, %3"
+      : "=v"(out), "=s"(carry)
+      : "v"(v), "s"(m));
+  return out;
+}
+
+// A run's state on its way down: the chosen texel, the ray's stretch inside it,
+// and the rays that still have a run.
+struct Stretch {
+  int x, y;
+  float u0, u1;
+  Lanes have;
+};
+
+// What the rays of a wavefront share on their way down: where they head, when
+// that is the same way for all of them, and (on the sphere) the quartic of each
+// ray's tip height, r(u) = a1 u + a2 u^2 + a3 u^3 + a4 u^4 + ..., the series of
+// |p + t L| - |p| with t = u / (1 - c u).
+struct Heading {
+  int ex, ey;  // 1: forward along the columns / rows, 0: backward
+  bool same;
+  float a2, a3, a4;
+};
+
+template <bool SPHERE>
+__device__ __forceinline__ Heading heading_of(const TileK& T, const Ray<SPHERE>& r) {
+  Heading d;
+  d.ex = __builtin_amdgcn_readfirstlane(r.sx > 0 ? 1 : 0);
+  d.ey = __builtin_amdgcn_readfirstlane(r.sy > 0 ? 1 : 0);
+  // (the bounds of the tip height's fit hold for origins within 5% of the radius
+  // whose path moves at least 0.95 of a texel per nominal texel of travel; how
+  // far a final sample lies from its base texel, for at most 1.09)
+  const float k2 = (r.Kx * r.Kx + r.Ky * r.Ky) * (4.0f * T.half_delta * T.half_delta);
+  d.same = lanes(!(r.sx == 2 * d.ex - 1 && r.sy == 2 * d.ey - 1 && fabsf(r.invKx) < 1e30f &&
+                   fabsf(r.invKy) < 1e30f &&
+                   (!SPHERE || (fabsf(r.hp + r.dz) * T.invR < 0.05f && k2 > 0.9f && k2 < 1.2f)))) == 0;
+  d.a2 = d.a3 = d.a4 = 0.0f;
+  if (SPHERE) {
+    const float k = r.cp * r.cp * r.invrho;
+    const float b2 = 0.5f * k, b3 = -0.5f * r.sp * k * r.invrho;
+    const float b4 = k * (5.0f * r.sp * r.sp - 1.0f) * 0.125f * r.invrho * r.invrho;
+    d.a2 = fmaf(r.sp, r.c, b2);
+    d.a3 = fmaf(r.c, fmaf(r.sp, r.c, 2.0f * b2), b3);
+    d.a4 = fmaf(r.c, fmaf(r.c, fmaf(r.sp, r.c, 3.0f * b2), 3.0f * b3), b4);
+  }
+  return d;
+}
+
+// The quartic's second-order expansion at the middle of a stretch, plus the
+// reference height: tip height above sea level ~ k0 + u (k1 + u k2).
+struct TipFit {
+  float k0, k1, k2;
+};
+
+template <bool SPHERE>
+__device__ __forceinline__ TipFit tip_fit(const Ray<SPHERE>& r, const Heading& d, float u0,
+                                          float u1) {
+  const float uc = 0.5f * (u0 + u1), w = uc * uc;
+  TipFit f;
+  f.k2 = fmaf(uc, fmaf(6.0f * d.a4, uc, 3.0f * d.a3), d.a2);
+  f.k1 = fmaf(-w, fmaf(8.0f * d.a4, uc, 3.0f * d.a3), r.sp);
+  f.k0 = fmaf(w * uc, fmaf(3.0f * d.a4, uc, d.a3), r.hp) + r.dz;
+  return f;
+}
+
+// One step of a descent for a wavefront whose rays head the same way: the ray
+// crosses up to three texels (before both lines, after the first, after both)
+// split at c1 <= c2, with maxima M0 .. M2 (-inf: no such texel, its bound is then
+// +inf).  Sets t1 (the second texel over the first) and t2 (the third over those)
+// and moves the stretch to the choice.
+//
+// The choice is the smallest of the texels' bounds, tip height less texel
+// maximum.  An exact tip height costs 11 operations with a root and a
+// reciprocal, and only the order of the bounds matters, so on the sphere they
+// are taken from the run's fit (two FMAs) and used when they differ by more than
+// the fit and the rounding can: err is twice the fit's bound, and heights carry
+// a few ulps of the bound itself.  A wavefront with a closer pair evaluates the
+// exact bounds, so the choices are those of the exact bounds in every case.
+// RISING: every tip rises along the run, so it is lowest where it enters a piece.
+// TOP: a first piece over a texel without a height (NaN) counts as absent, as in
+// the walk of descend_apart; further down it ends the run.
+template <bool SPHERE, bool RISING, bool TOP>
+__device__ __forceinline__ void pick_piece(const TileK& T, const Ray<SPHERE>& r, const TipFit& f,
+                                           float err, float M0, float M1, float M2, float c1,
+                                           float c2, Stretch& st, Lanes& t1, Lanes& t2,
+                                           unsigned& n_lb) {
+  // where the tip is lowest on each piece
+  const float p0 = RISING ? st.u0 : __builtin_amdgcn_fmed3f(r.uhmin, st.u0, c1);
+  const float p1 = RISING ? c1 : __builtin_amdgcn_fmed3f(r.uhmin, c1, c2);
+  const float p2 = RISING ? c2 : __builtin_amdgcn_fmed3f(r.uhmin, c2, st.u1);
+  const bool ok0 = c1 > st.u0, ok1 = c2 > c1, ok2 = st.u1 > c2;
+  float lb0, lb1, lb2, b01, n0, n1;
+  Lanes found;
+  auto order = [&](float v0, float v1, float v2) {
+    // an absent piece has bound +inf
+    lb0 = ok0 ? v0 : SS_INF;
+    if (TOP) lb0 = v0 == v0 ? lb0 : SS_INF;
+    lb1 = ok1 ? v1 : SS_INF;
+    lb2 = ok2 ? v2 : SS_INF;
+    // strict argmin from the far end == '<=' from the near end
+    const bool s1 = lb1 <= lb0;
+    b01 = s1 ? lb1 : lb0;
+    const bool s2 = lb2 <= b01;
+    t1 = lanes(s1);
+    t2 = lanes(s2);
+    found = lanes((s2 ? lb2 : b01) < SS_INF);
+    n0 = s2 ? c2 : (s1 ? c1 : st.u0);
+    n1 = s2 ? st.u1 : (s1 ? c2 : c1);
+  };
+  if (SPHERE) {
+    order(fmaf(p0, fmaf(p0, f.k2, f.k1), f.k0 - M0), fmaf(p1, fmaf(p1, f.k2, f.k1), f.k0 - M1),
+          fmaf(p2, fmaf(p2, f.k2, f.k1), f.k0 - M2));
+    const float close = fmaf(fabsf(b01), 1e-6f, err);
+    const Lanes unsure = lanes(fabsf(lb1 - lb0) < close) | lanes(fabsf(lb2 - b01) < close);
+    if (unsure & st.have)
+      order(tip_rise_u(r, T, p0) - (M0 - r.hp), tip_rise_u(r, T, p1) - (M1 - r.hp),
+            tip_rise_u(r, T, p2) - (M2 - r.hp));
+  } else {
+    order(tip_rise_u(r, T, p0) - (M0 - r.hp), tip_rise_u(r, T, p1) - (M1 - r.hp),
+          tip_rise_u(r, T, p2) - (M2 - r.hp));
+  }
+  n_lb += (ok0 && M0 != -SS_INF ? 1u : 0u) + (ok1 && M1 != -SS_INF ? 1u : 0u) +
+          (ok2 && M2 != -SS_INF ? 1u : 0u);
+  st.have &= found;
+  st.u0 = n0;
+  st.u1 = n1;
+}
+
+// True when no sample a descent can still reach from the level-lv texel of st
+// matters: they all clear `need` (clears) over the highest terrain their taps can
+// touch.  The samples lie within 0.83 texel of the base texel's stretch and their
+// taps within two texels of the base texel, so the two by two texels one level up
+// that surround the chosen texel by half its size hold every tap (lv >= 1).
+template <bool SPHERE>
+__device__ __forceinline__ bool out_of_reach(const TileK& T, const Ray<SPHERE>& r, const Level& up,
+                                             const Stretch& st, float need) {
+  const int x = min(max((st.x - 1) >> 1, 0), up.w - 2);
+  const int y = min(max((st.y - 1) >> 1, 0), up.h - 2);
+  const unsigned a = 4u * (unsigned)(__mul24(y, up.w) + x);
+  const f32x2 p = pair_at(up, a), q = pair_at(up, a + 4u * (unsigned)up.w);
+  const float M = fmaxf(fmaxf(p.x, p.y), fmaxf(q.x, q.y));
+  const float t0 = fmaxf(M, r.hp) - r.hp;
+  const float tlo = fmaxf(T.half_delta, u_to_t(r, st.u0) - 1.75f * T.half_delta);
+  return clears(r, T, tlo, r.dz > t0 ? r.dz : t0, need);
+}
+
+// The descent of a run for such a wavefront, from the level-m texel (cx, cy)
+// under u = ua whose lines ahead lie at ux, uy; no ray crosses a second line of
+// either axis before ub (a run is one level-m texel of travel long, so a second
+// crossing is rare; such a wavefront takes descend_apart).  The levels run in step over the wavefront (a ray that
+// has lost its run only idles), so the loop and each level's geometry are scalar.
+// EX: the columns run forward.
+//
+// Bound by instruction issue and by gathers (16 address cycles each), so a level
+// reads its four children as two pairs and takes about 50 instructions where the
+// walk in descend_apart takes 105 and three gathers, and the top texels one step
+// where the walk takes up to four.  On the 8 suns of a 4096^2 tile: 10.85 ms with
+// that walk, 9.16 with this descent, 6.76 with the early end below.
+//
+// A run ends early once nothing below the chosen texel can matter
+// (out_of_reach), tested three and five levels below the top: most runs of lit
+// rays pass far above their terrain.  The four maxima around the texel cost two
+// loads and about 35 instructions, a level two and 50, the final samples six and 150.
+// Tested earlier the bound is too coarse, and more tests cost more than they end.
+template <bool SPHERE, bool RISING, bool EX>
+__device__ __forceinline__ void descend_together(const TileK& T, const Ray<SPHERE>& r,
+                                                 const Heading& d, unsigned errs, int m, int cx,
+                                                 int cy, float ux, float uy, float ua, float ub,
+                                                 float need, Stretch& st, unsigned& n_lb) {
+  const Level Lt = level_of(T, m);
+  LevelK next = T.lev[m - 1];
+  const int sx = EX ? 1 : -1, sy = 2 * d.ey - 1;
+  const Lanes flipx = EX ? 0 : ~0ull, flipy = d.ey ? 0 : ~0ull;
+  TipFit f{0.0f, 0.0f, 0.0f};
+  if (SPHERE) f = tip_fit(r, d, ua, ub);
+  float err = fit_err_top(errs);
+  asm("" : "+v"(err));  // beside a literal, a second scalar operand costs a move
+  Lanes t1, t2;
+  {
+    const Lanes xfirst = lanes(ux <= uy);
+    const float c1 = __builtin_amdgcn_fmed3f(of(xfirst) ? ux : uy, ua, ub);
+    const float c2 = __builtin_amdgcn_fmed3f(of(xfirst) ? uy : ux, ua, ub);
+    const int cx1 = cx + sx, cy1 = cy + sy;
+    const Lanes x0 = lanes((unsigned)cx < (unsigned)Lt.w), x1 = lanes((unsigned)cx1 < (unsigned)Lt.w);
+    const Lanes y0 = lanes((unsigned)cy < (unsigned)Lt.h), y1 = lanes((unsigned)cy1 < (unsigned)Lt.h);
+    st.u0 = ua;
+    st.u1 = ub;
+    st.have = lanes(true);
+    const unsigned a = 4u * (unsigned)(__mul24(cy, Lt.w) + cx), ay = a + (unsigned)(4 * sy * Lt.w);
+    float M0 = value_at(Lt, a);
+    float M1 = value_at(Lt, of(xfirst) ? a + (unsigned)(4 * sx) : ay);
+    float M2 = value_at(Lt, ay + (unsigned)(4 * sx));
+    M0 = of(x0 & y0) ? M0 : -SS_INF;
+    M1 = of((xfirst & x1 & y0) | (~xfirst & x0 & y1)) ? M1 : -SS_INF;
+    M2 = of(x1 & y1) ? M2 : -SS_INF;
+    pick_piece<SPHERE, RISING, true>(T, r, f, err, M0, M1, M2, c1, c2, st, t1, t2, n_lb);
+    st.x = of(t2 | (t1 & xfirst)) ? cx1 : cx;
+    st.y = of(t2 | (t1 & ~xfirst)) ? cy1 : cy;
+  }
+  // low edge of the chosen texel relative to the origin texel centre, in texels
+  float fx = (float)((st.x << m) - r.i) - 0.5f - r.ox;
+  float fy = (float)((st.y << m) - r.j) - 0.5f - r.oy;
+  int lv = m, stop = max(m - 3, 0);
+  for (int part = 0;; ++part) {
+#pragma clang loop unroll(disable)
+    for (; lv > stop; --lv) {
+      const Level L = level_from(next);
+      next = T.lev[max(lv - 2, 0)];  // the next level's geometry, ahead of its use
+      const float fh = __builtin_bit_cast(float, (126 + lv) << 23);  // 2^(lv - 1)
+      const float mxr = fx + fh, myr = fy + fh;  // mid-lines (exact at texel centres)
+      const float umx = mxr * r.invKx, umy = myr * r.invKy;
+      const Lanes xfirst = lanes(umx <= umy);
+      const float c1 = __builtin_amdgcn_fmed3f(of(xfirst) ? umx : umy, st.u0, st.u1);
+      const float c2 = __builtin_amdgcn_fmed3f(of(xfirst) ? umy : umx, st.u0, st.u1);
+      // the rows of children before and after the mid-line
+      const unsigned a = (unsigned)__mul24(st.y, 8 * L.w) + 8u * (unsigned)st.x;
+      const unsigned ra = a + (unsigned)(d.ey ? 0 : 4 * L.w), rc = a + (unsigned)(d.ey ? 4 * L.w : 0);
+      float M0, Mx, My, M2;
+      if (((L.w | L.h) & 1) == 0) {
+        const f32x2 p = pair_at(L, ra), q = pair_at(L, rc);
+        M0 = EX ? p.x : p.y;
+        Mx = EX ? p.y : p.x;
+        My = EX ? q.x : q.y;
+        M2 = EX ? q.y : q.x;
+      } else {
+        // children beyond a ragged edge are absent: only the high ones can be.  (A
+        // pair could end past the level there: single loads, kept apart.)
+        const Lanes hx = lanes(2 * st.x + 1 < L.w) | flipx, hy = lanes(2 * st.y + 1 < L.h) | flipy;
+        const Lanes lx = lanes(2 * st.x + 1 < L.w) | ~flipx, ly = lanes(2 * st.y + 1 < L.h) | ~flipy;
+        unsigned r1 = ra + 4u, r3 = rc + 4u;
+        asm("" : "+v"(r1), "+v"(r3));
+        const float p0 = value_at(L, ra), p1 = value_at(L, r1), q0 = value_at(L, rc), q1 = value_at(L, r3);
+        M0 = of(lx & ly) ? (EX ? p0 : p1) : -SS_INF;
+        Mx = of(hx & ly) ? (EX ? p1 : p0) : -SS_INF;
+        My = of(lx & hy) ? (EX ? q0 : q1) : -SS_INF;
+        M2 = of(hx & hy) ? (EX ? q1 : q0) : -SS_INF;
+      }
+      pick_piece<SPHERE, RISING, false>(T, r, f, err, M0, of(xfirst) ? Mx : My, M2, c1, c2, st, t1,
+                                        t2, n_lb);
+      // child bits: flipped on an axis whose mid-line the chosen piece lies beyond
+      const Lanes mx = (t2 | (t1 & xfirst)) ^ flipx, my = (t2 | (t1 & ~xfirst)) ^ flipy;
+      st.x = twice_plus(st.x, mx);
+      st.y = twice_plus(st.y, my);
+      fx = of(mx) ? mxr : fx;
+      fy = of(my) ? myr : fy;
+    }
+    if (lv == 0) return;
+    if (lv >= 2 && T.prune) {
+      const Level up = level_of(T, lv + 1);
+      if (up.w >= 2 && up.h >= 2) {
+        st.have &= ~lanes(out_of_reach(T, r, up, st, need));
+        if (st.have == 0) return;
+      }
+    }
+    if (SPHERE && part == 0 && m >= SS_REFIT_FROM) {
+      f = tip_fit(r, d, st.u0, st.u1);
+      err = fit_err_low(errs);
+      asm("" : "+v"(err));
+    }
+    stop = part == 0 ? max(m - 5, 0) : 0;
+  }
+}
+
+// The descent of a run for any wavefront: a walk over the level-m texels crossed
+// for u in [ua, ub] (gx, gy: the grid lines ahead of the first, (cx, cy)), then
+// the children of the chosen one.
+template <bool SPHERE>
+__device__ __forceinline__ void descend_apart(const TileK& T, const Ray<SPHERE>& r, int m, int cx,
+                                              int cy, float gx, float gy, float ua, float ub,
+                                              bool& found, Stretch& st, unsigned& n_lb) {
+  found = false;
   const int S = 1 << m;
   const bool rising = r.uhmin <= ua;  // tip height grows over the whole run
-  // the next grid line ahead of the current texel on each axis (+1 when the
-  // path moves forward or not at all)
   const int ex = r.Kx >= 0.0f ? 1 : 0, ey = r.Ky >= 0.0f ? 1 : 0;
-  // top level: walk the level-m texels crossed for u in [ua, ub]
-  int cx = (r.i >> m) + (int)floorf(ldexpf((float)(r.i & (S - 1)) + 0.5f + r.ox + r.Kx * ua, -m));
-  int cy = (r.j >> m) + (int)floorf(ldexpf((float)(r.j & (S - 1)) + 0.5f + r.oy + r.Ky * ua, -m));
-  // those grid lines relative to the origin texel centre, in texels; they
-  // are half-integers, exact in FP32, and move by +-2^m per step
-  float gx = (float)(((cx + ex) << m) - r.i) - 0.5f - r.ox;
-  float gy = (float)(((cy + ey) << m) - r.j) - 0.5f - r.oy;
   const float stx = (float)(r.sx * S), sty = (float)(r.sy * S);
   const Level Ltop = level_of(T, m);
-  const unsigned lwm = (unsigned)T.lw[m], lhm = (unsigned)T.lh[m];
+  const unsigned lwm = (unsigned)Ltop.w, lhm = (unsigned)Ltop.h;
   float best = SS_INF, bu0 = ua, bu1 = ua, brise = 0.0f;
   int bx = cx, by = cy, have = 0;
   float u0 = ua;
@@ -387,7 +758,7 @@ __device__ __forceinline__ void descend_run(const TileK& T, const Ray<SPHERE>& r
     }
     // children beyond a ragged edge are absent; px and py always exist, so
     // only the high children px + 1, py + 1 can be missing
-    const bool hx = px + 1 < T.lw[lv - 1], hy = py + 1 < T.lh[lv - 1];
+    const bool hx = px + 1 < Lc.w, hy = py + 1 < Lc.h;
     const bool ina = (ex == 1 || hx) && (ey == 1 || hy);  // before both
     const bool inc = (ex == 0 || hx) && (ey == 0 || hy);  // after both
     const bool inb = xfirst ? ((ex == 0 || hx) && (ey == 1 || hy)) : ((ex == 1 || hx) && (ey == 0 || hy));
@@ -416,37 +787,75 @@ __device__ __forceinline__ void descend_run(const TileK& T, const Ray<SPHERE>& r
     bu0 = nu0;
     bu1 = nu1;
   }
+  st = Stretch{bx, by, bu0, bu1, 0};
+  found = true;
+}
+
+// One concatenated run (Sec. 3.3): descent from level m0 = run_m0(T.run[j]) over the
+// texels the ray crosses (Sec. 3.2, Fig. 3b), strict argmin from the far end
+// (kept here as '<=' scanning from the near end), then three samples half a
+// texel apart around the chosen base texel (Alg. 1, final level).
+template <bool SPHERE>
+__device__ __forceinline__ void descend_run(const TileK& T, const Ray<SPHERE>& r, const Heading& d,
+                                            int jseg, float need, SegOut& out, unsigned& n_lb,
+                                            unsigned& n_smp) {
+  out.valid = 0;
+  const float ta = T.tau[jseg], tb = T.tau[jseg + 1];
+  const float ua = t_to_u(r, ta);
+  const float ub = fminf(t_to_u(r, tb), r.uexit);
+  const int m = run_m0(T.run[jseg]);
+  const int S = 1 << m;
+  // the next grid line ahead of the current texel on each axis (+1 when the
+  // path moves forward or not at all)
+  const int ex = r.Kx >= 0.0f ? 1 : 0, ey = r.Ky >= 0.0f ? 1 : 0;
+  // top level: the level-m texel under u = ua
+  const int cx = (r.i >> m) + (int)floorf(ldexpf((float)(r.i & (S - 1)) + 0.5f + r.ox + r.Kx * ua, -m));
+  const int cy = (r.j >> m) + (int)floorf(ldexpf((float)(r.j & (S - 1)) + 0.5f + r.oy + r.Ky * ua, -m));
+  // those grid lines relative to the origin texel centre, in texels; they
+  // are half-integers, exact in FP32, and move by +-2^m per step
+  const float gx = (float)(((cx + ex) << m) - r.i) - 0.5f - r.ox;
+  const float gy = (float)(((cy + ey) << m) - r.j) - 0.5f - r.oy;
+  const float ux = gx * r.invKx, uy = gy * r.invKy;
+  const float ux2 = (gx + (float)(r.sx * S)) * r.invKx, uy2 = (gy + (float)(r.sy * S)) * r.invKy;
+  const unsigned errs = jseg < SS_FITRUNS ? T.fit_err[jseg] : SS_FIT_NONE;
+  Stretch st;
+  if (d.same && m > 0 && errs != SS_FIT_NONE && lanes(fminf(ux2, uy2) < ub) == 0) {
+    const bool rising = lanes(!(r.uhmin <= ua)) == 0;
+    if (rising && d.ex)
+      descend_together<SPHERE, true, true>(T, r, d, errs, m, cx, cy, ux, uy, ua, ub, need, st, n_lb);
+    else if (rising)
+      descend_together<SPHERE, true, false>(T, r, d, errs, m, cx, cy, ux, uy, ua, ub, need, st, n_lb);
+    else if (d.ex)
+      descend_together<SPHERE, false, true>(T, r, d, errs, m, cx, cy, ux, uy, ua, ub, need, st, n_lb);
+    else
+      descend_together<SPHERE, false, false>(T, r, d, errs, m, cx, cy, ux, uy, ua, ub, need, st, n_lb);
+  } else {
+    bool found;
+    descend_apart(T, r, m, cx, cy, gx, gy, ua, ub, found, st, n_lb);
+    st.have = lanes(found);
+  }
+  if (st.have == 0) return;
   // final samples on the half-texel grid t_n = (n + 1) delta/2 around the
   // middle of the base texel's stretch of ray
-  const float tin = u_to_t(r, bu0), tout = u_to_t(r, bu1);
+  const float tin = u_to_t(r, st.u0), tout = u_to_t(r, st.u1);
   const float tmid = 0.5f * (tin + tout);
-  const int nc = (int)floorf((tmid - T.half_delta) * T.two_over_delta + 0.5f);
-  float bdh = SS_INF, bt = 0.0f, bu = 0.0f;
-  int found = 0, bn = -1;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const int n = nc - 1 + k;
-    const float t = (float)(n + 1) * T.half_delta;
-    const float u = t_to_u(r, t);
-    if (n >= 0 && u < r.uexit) {
-      const Sample s = sample_at(r, T, t, u);
-      n_smp++;
-      if (s.dh <= bdh) {
-        bdh = s.dh;
-        bt = t;
-        bu = u;
-        bn = n;
-        found = 1;
-      }
-    }
-  }
-  if (!found) return;
+  const float ncf = floorf((tmid - T.half_delta) * T.two_over_delta + 0.5f);
+  // the samples lie within 3/4 texel of that middle, their taps two texels
+  // around the base texel
+  const bool in = T.W >= 7 && T.H >= 7 && (unsigned)(st.x - 3) <= (unsigned)(T.W - 7) &&
+                  (unsigned)(st.y - 3) <= (unsigned)(T.H - 7);
+  Deepest s;
+  if ((lanes(!in) & st.have) == 0)
+    s = samples_inside(T, r, ncf, n_smp);
+  else
+    s = samples_any(T, r, ncf, n_smp);
+  if (!(of(st.have) && s.found)) return;
   float num, den;
-  clearance_terms(r, bt, bdh, num, den);
+  clearance_terms(r, s.t, s.dh, num, den);
   out.key = tangent_key(num, den);
-  out.t = bt;
-  out.u = bu;
-  out.n = bn;
+  out.t = s.t;
+  out.u = s.u;
+  out.n = s.n;
   out.valid = 1;
 }
 
@@ -464,8 +873,8 @@ template <bool SPHERE>
 __device__ __forceinline__ void point_run(const TileK& T, const Ray<SPHERE>& r, int jseg,
                                           SegOut& out, unsigned& n_lb, unsigned& n_smp) {
   out.valid = 0;
-  const int m0 = T.m0[jseg];
-  const int a = T.a0[jseg];
+  const int m0 = run_m0(T.run[jseg]);
+  const int a = run_a0(T.run[jseg]);
   int K = 2 << m0;
   for (int m = m0; m >= 1; --m) {
     const int step = 1 << m;
@@ -480,7 +889,7 @@ __device__ __forceinline__ void point_run(const TileK& T, const Ray<SPHERE>& r, 
       // texel under the tip (positions before the edge are >= 0 by construction)
       const int cx = (int)floorf((float)r.i + 0.5f + r.ox + r.Kx * u) >> m;
       const int cy = (int)floorf((float)r.j + 0.5f + r.oy + r.Ky * u) >> m;
-      const bool ok = u < r.uexit && (unsigned)cx < (unsigned)T.lw[m] && (unsigned)cy < (unsigned)T.lh[m];
+      const bool ok = u < r.uexit && (unsigned)cx < (unsigned)Lm.w && (unsigned)cy < (unsigned)Lm.h;
       const float v = tip_rise(r, T, t) - (level_at(Lm, cx, cy) - r.hp);
       n_lb += ok ? 1u : 0u;
       const bool take = ok && v < best;
@@ -518,28 +927,6 @@ __device__ __forceinline__ void point_run(const TileK& T, const Ray<SPHERE>& r, 
   out.valid = 1;
 }
 
-// True when every sample at ray length >= t clears the angle whose tangent is
-// need_tan (an angle in (-pi/2, pi/2)), given that no terrain rises above
-// `top` (relative to the reference height hp, and at least the origin's dz,
-// i.e. not below the origin): the clearance of the point at that height below
-// the tip grows with t on the plane and on the sphere.  Used for the
-// result-invariant early exits.
-template <bool SPHERE>
-__device__ __forceinline__ bool clears(const Ray<SPHERE>& r, const TileK& T, float t, float top,
-                                       float need_tan) {
-  const float d = tip_rise(r, T, t) - top;
-  if (!(d > 0.0f)) return false;
-  float num, den;
-  clearance_terms(r, t, d, num, den);
-  return den <= 0.0f || num >= need_tan * den;  // den <= 0: at least pi/2
-}
-
-// tan(min(alpha, r_L) + margin) for the tangent key of alpha (tan addition).
-__device__ __forceinline__ float need_tangent(const TileK& T, float key) {
-  const float k = fmaxf(fminf(key, T.tan_rL), -1e30f);
-  return (k + T.tan_margin) * ss_rcp(1.0f - k * T.tan_margin);
-}
-
 struct RayResult {
   float alpha;
   float key;      // tangent key of alpha (orders like alpha)
@@ -564,6 +951,8 @@ __device__ __forceinline__ RayResult shadow_dp(const TileK& T, const Ray<SPHERE>
   res.valid = 0;
   float best = SS_INF;                    // tangent key of the smallest clearance so far
   float need = need_tangent(T, SS_INF);   // tan(min(alpha, r_L) + margin)
+  Heading way{};
+  if (!POINT) way = heading_of(T, r);
   for (int j = 0; j < T.nseg; ++j) {
     const float ta = T.tau[j];
     if (!(t_to_u(r, ta) < r.uexit)) break;  // the run starts outside the tile
@@ -576,7 +965,7 @@ __device__ __forceinline__ RayResult shadow_dp(const TileK& T, const Ray<SPHERE>
     if (POINT)
       point_run(T, r, j, so, n_lb, n_smp);
     else
-      descend_run(T, r, j, so, n_lb, n_smp);
+      descend_run(T, r, way, j, need, so, n_lb, n_smp);
     if (so.valid && so.key < best) {
       best = so.key;
       res.t = so.t;
@@ -644,7 +1033,8 @@ __device__ __forceinline__ RayResult shadow_uniform(const TileK& T, const Ray<SP
 // offset from the kernel arguments would put a dependent memory load before
 // every bound; kernels that run the walk copy the offsets to LDS first.
 __device__ __forceinline__ void bound_tab_fill(const TileK& T, int* tab) {
-  if (threadIdx.x < SS_MAXLEV) tab[threadIdx.x] = T.loff[threadIdx.x];
+  if (threadIdx.x >= 1 && threadIdx.x < (unsigned)T.L)
+    tab[threadIdx.x] = (int)(T.lev[threadIdx.x].p - T.mm);
 }
 
 __device__ __forceinline__ float bound_at(const TileK& T, const int* tab, int m, int cx, int cy) {

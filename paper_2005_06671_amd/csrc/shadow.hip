@@ -48,7 +48,7 @@ __device__ __forceinline__ void ray_coords(int nbx, int nblocks, int grp, int& i
 enum { FWD_PLAIN = 0, FWD_COUNT = 1, FWD_SAVE = 2 };
 
 template <bool SPHERE, int TW, int MODE, int FLAGS>
-__global__ __launch_bounds__(256) void shadow_kernel(TileK T, float* __restrict__ out,
+SS_RAY_KERNEL void shadow_kernel(TileK T, float* __restrict__ out,
                                                      unsigned long long* counter,
                                                      int* __restrict__ sample, int nbx,
                                                      int nblocks) {
@@ -264,7 +264,7 @@ struct AdjBlocks {
 };
 
 template <bool SPHERE, int TW, int MODE, bool SAVED>
-__global__ __launch_bounds__(256) void adjoint_kernel(TileK T, SunTrig st,
+SS_RAY_KERNEL void adjoint_kernel(TileK T, SunTrig st,
                                                       const float* __restrict__ gs,
                                                       const int* __restrict__ sample,
                                                       const float* __restrict__ sfwd,
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256) void adjoint_kernel(TileK T, SunTrig st,
 #define SS_PEN_BLOCKS 8
 
 template <bool SPHERE, int MODE>
-__global__ __launch_bounds__(256) void adjoint_penumbra_kernel(TileK T, SunTrig st,
+SS_RAY_KERNEL void adjoint_penumbra_kernel(TileK T, SunTrig st,
                                                                const float* __restrict__ gs,
                                                                const float* __restrict__ sfwd,
                                                                float* __restrict__ gh,
@@ -400,7 +400,7 @@ __device__ __forceinline__ float shade_point(const TileK& T, float2 q, const int
 // neighbours on the terrain, so their shadow rays walk the same cells (a row
 // of 64 pixels spreads them out).  Otherwise lane k takes point k.
 template <bool SPHERE, int MODE, bool IMAGE>
-__global__ __launch_bounds__(256) void points_kernel(TileK T, const float2* __restrict__ xy,
+SS_RAY_KERNEL void points_kernel(TileK T, const float2* __restrict__ xy,
                                                      long long n, int img_w, int nbx,
                                                      float* __restrict__ out) {
   __shared__ int tab[SS_MAXLEV];
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(256) void points_kernel(TileK T, const float2* __re
 // Work is mapped as in points_kernel; the sun gradient is reduced per
 // workgroup as in adjoint_kernel.
 template <bool SPHERE, int MODE, bool IMAGE>
-__global__ __launch_bounds__(256) void points_adjoint_kernel(TileK T, SunTrig st,
+SS_RAY_KERNEL void points_adjoint_kernel(TileK T, SunTrig st,
                                                              const float2* __restrict__ xy,
                                                              long long n, int img_w, int nbx,
                                                              const float* __restrict__ gs,
