@@ -122,6 +122,38 @@ __host__ __device__ inline float run_start_len(int a, double half_delta) {
   return (float)((double)(a + 1) * half_delta);
 }
 
+#ifdef __HIP_DEVICE_COMPILE__
+#define SS_RCP_SEED(x) __builtin_amdgcn_rcpf(x)
+#define SS_RSQ_SEED(x) __builtin_amdgcn_rsqf(x)
+#else  // the host pass only parses the kernels
+#define SS_RCP_SEED(x) (1.0f / (x))
+#define SS_RSQ_SEED(x) (1.0f / sqrtf(x))
+#endif
+
+// The correctly rounded reciprocal, root and quotient, as 1.0f / x, sqrtf(x) and
+// a / b give them, where operands and results are normal numbers with exponents
+// well inside the range: without the scaling and special cases of the general
+// sequences they take 3, 5 and 5 (given y = rcp_rn(b)) instructions in place of
+// 11, 16 and 11.  The hardware's reciprocal and reciprocal root are within an
+// ulp; one Newton step rounds correctly for every mantissa (all 2^24 of two
+// adjacent exponents compared with the general forms on gfx950, at seven places
+// of the range).  The quotient follows from a correctly rounded y by Markstein's
+// theorem: after the first correction q is within an ulp, after the second it is
+// rounded correctly.
+__device__ inline float rcp_rn(float x) {
+  const float y = SS_RCP_SEED(x);
+  return fmaf(fmaf(-x, y, 1.0f), y, y);
+}
+__device__ inline float sqrt_rn(float x) {
+  const float y = SS_RSQ_SEED(x), s = x * y;
+  return fmaf(fmaf(-s, s, x), 0.5f * y, s);
+}
+__device__ inline float div_rn(float a, float b, float y) {
+  float q = a * y;
+  q = fmaf(fmaf(-b, q, a), y, q);
+  return fmaf(fmaf(-b, q, a), y, q);
+}
+
 // Ray tile shapes: lanes of one wavefront cover TW x TH texels (TW * TH = 64),
 // a 256-thread workgroup covers 2 x 2 wavefront tiles.
 enum { SS_TILE_8x8 = 1, SS_TILE_16x4 = 2, SS_TILE_4x16 = 3, SS_TILE_32x2 = 4 };
