@@ -62,9 +62,16 @@ struct Ray {
 // shifted by (ox, oy); heights relative to hp, a stored height, with the
 // origin dz above it.  At centres ox = oy = dz = -0, which every sum below
 // drops exactly, so those rays compute as if the terms were absent.
-template <bool SPHERE>
-__device__ __forceinline__ void ray_init(const TileK& T, int i, int j, float hp, Ray<SPHERE>& r,
-                                         float ox = -0.0f, float oy = -0.0f, float dz = -0.0f) {
+//
+// NORMAL: divisions and roots by their short exact forms (rcp_rn), the same bits
+// for the origins ray_init lets through; without them the set-up took a tenth of a
+// descent ray's instructions.
+template <bool SPHERE, bool NORMAL>
+__device__ __forceinline__ void ray_init_as(const TileK& T, int i, int j, float hp, Ray<SPHERE>& r,
+                                            float ox, float oy, float dz) {
+  auto inv = [](float x) { return NORMAL ? rcp_rn(x) : 1.0f / x; };
+  auto quot = [](float p, float q, float iq) { return NORMAL ? div_rn(p, q, iq) : p / q; };
+  auto root = [](float x) { return NORMAL ? sqrt_rn(x) : sqrtf(x); };
   r.i = i;
   r.j = j;
   r.ox = ox;
@@ -76,17 +83,18 @@ __device__ __forceinline__ void ray_init(const TileK& T, int i, int j, float hp,
   if (SPHERE) {
     // n = (a, b, 1)/g with a = X/R, b = Y/R, g = |(a, b, 1)|; rho = R (1 + h_p/R)
     const float a = X * T.invR, b = Y * T.invR;
-    const float g = sqrtf(1.0f + a * a + b * b);
-    const float ig = 1.0f / g;
+    const float g = root(1.0f + a * a + b * b);
+    const float ig = inv(g);
     const float r1 = 1.0f + (hp + dz) * T.invR;
     r.sp = (a * T.Lx + b * T.Ly + T.Lz) * ig;
     const float cx = b * T.Lz - T.Ly, cy = T.Lx - a * T.Lz, cz = a * T.Ly - b * T.Lx;
-    r.cp = sqrtf(cx * cx + cy * cy + cz * cz) * ig;
-    const float sc = g / (r1 * T.texel);
+    r.cp = root(cx * cx + cy * cy + cz * cz) * ig;
+    const float rt = r1 * T.texel, ir1 = inv(r1);
+    const float sc = quot(g, rt, inv(rt));
     r.Kx = (T.Lx - a * T.Lz) * sc;
     r.Ky = (T.Ly - b * T.Lz) * sc;
-    r.c = T.Lz * g / r1 * T.invR;
-    r.invrho = T.invR / r1;
+    r.c = quot(T.Lz * g, r1, ir1) * T.invR;
+    r.invrho = quot(T.invR, r1, ir1);
     // |p + t L| is smallest at t = -rho s (ahead of p only when the sun is
     // below the local horizon)
     if (r.sp < 0.0f) {
@@ -109,16 +117,27 @@ __device__ __forceinline__ void ray_init(const TileK& T, int i, int j, float hp,
   r.sy = r.Ky > 0.0f ? 1 : (r.Ky < 0.0f ? -1 : 0);
   // +inf on an axis the path never moves along: every crossing time on it is
   // then +-inf (the numerators are half-integers, never 0)
-  r.invKx = r.sx ? 1.0f / r.Kx : SS_INF;
-  r.invKy = r.sy ? 1.0f / r.Ky : SS_INF;
+  r.invKx = r.sx ? inv(r.Kx) : SS_INF;
+  r.invKy = r.sy ? inv(r.Ky) : SS_INF;
   // leaving the tile: first boundary in the direction of travel
-  float ux = SS_INF, uy = SS_INF;
-  if (r.sx > 0) ux = ((float)(T.W - i) - 0.5f - ox) / r.Kx;
-  if (r.sx < 0) ux = ((float)(-i) - 0.5f - ox) / r.Kx;
-  if (r.sy > 0) uy = ((float)(T.H - j) - 0.5f - oy) / r.Ky;
-  if (r.sy < 0) uy = ((float)(-j) - 0.5f - oy) / r.Ky;
+  const float ex = (float)(r.sx > 0 ? T.W - i : -i) - 0.5f - ox;
+  const float ey = (float)(r.sy > 0 ? T.H - j : -j) - 0.5f - oy;
+  const float ux = r.sx ? quot(ex, r.Kx, r.invKx) : SS_INF;
+  const float uy = r.sy ? quot(ey, r.Ky, r.invKy) : SS_INF;
   r.uexit = fminf(ux, uy);
 }
+
+template <bool SPHERE>
+__device__ __forceinline__ void ray_init(const TileK& T, int i, int j, float hp, Ray<SPHERE>& r,
+                                         float ox = -0.0f, float oy = -0.0f, float dz = -0.0f) {
+  ray_init_as<SPHERE, true>(T, i, j, hp, r, ox, oy, dz);
+  // every operand and result of the short forms is an ordinary number: an origin
+  // near the surface, a sun off its zenith, a path that moves along both axes
+  const bool ok = fabsf(r.hp + r.dz) * T.invR < 0.5f && r.cp > 1e-9f && r.cp < 2.0f &&
+                  fabsf(r.invKx) < 1e30f && fabsf(r.invKy) < 1e30f;
+  if (!ok) ray_init_as<SPHERE, false>(T, i, j, hp, r, ox, oy, dz);
+}
+
 
 template <bool SPHERE>
 __device__ __forceinline__ float u_to_t(const Ray<SPHERE>& r, float u) {
@@ -940,10 +959,12 @@ __device__ __forceinline__ float angle_of(float key) {
 }
 
 // Smallest clearance over the concatenated runs (Sec. 3.3), each by the
-// texel descent (POINT = false) or Alg. 1's point samples (POINT = true).
+// texel descent (POINT = false) or Alg. 1's point samples (POINT = true): over runs
+// j0, j0 + stride, ...
 template <bool SPHERE, bool POINT = false>
 __device__ __forceinline__ RayResult shadow_dp(const TileK& T, const Ray<SPHERE>& r, float top,
-                                               unsigned& n_lb, unsigned& n_smp) {
+                                               unsigned& n_lb, unsigned& n_smp, int j0 = 0,
+                                               int stride = 1) {
   RayResult res;
   res.t = 0.0f;
   res.u = 0.0f;
@@ -953,7 +974,7 @@ __device__ __forceinline__ RayResult shadow_dp(const TileK& T, const Ray<SPHERE>
   float need = need_tangent(T, SS_INF);   // tan(min(alpha, r_L) + margin)
   Heading way{};
   if (!POINT) way = heading_of(T, r);
-  for (int j = 0; j < T.nseg; ++j) {
+  for (int j = j0; j < T.nseg; j += stride) {
     const float ta = T.tau[j];
     if (!(t_to_u(r, ta) < r.uexit)) break;  // the run starts outside the tile
     if (T.prune) {
@@ -1147,13 +1168,18 @@ __device__ __forceinline__ RayResult shadow_exact(const TileK& T, const Ray<SPHE
   return res;
 }
 
+// No terrain rises above this (relative to h_p, at least 0).
+template <bool SPHERE>
+__device__ __forceinline__ float terrain_top(const TileK& T, const Ray<SPHERE>& r) {
+  const float t0 = T.prune ? fmaxf(mip_at(T, T.L - 1, 0, 0), r.hp) - r.hp : 0.0f;
+  return r.dz > t0 ? r.dz : t0;
+}
+
 // The shadow clearance of one ray by the chosen method.
 template <bool SPHERE, int MODE>
 __device__ __forceinline__ RayResult trace_ray(const TileK& T, const Ray<SPHERE>& r, unsigned& n_lb,
                                                unsigned& n_smp, const int* tab) {
-  // no terrain rises above `top` (relative to h_p, at least 0)
-  const float t0 = T.prune ? fmaxf(mip_at(T, T.L - 1, 0, 0), r.hp) - r.hp : 0.0f;
-  const float top = r.dz > t0 ? r.dz : t0;
+  const float top = terrain_top(T, r);
   if (MODE == SS_MODE_EXACT) return shadow_exact(T, r, top, n_lb, n_smp, tab);
   if (MODE == SS_MODE_POINT) return shadow_dp<SPHERE, true>(T, r, top, n_lb, n_smp);
   if (MODE == SS_MODE_UNIFORM) return shadow_uniform(T, r, top, n_smp);

@@ -79,6 +79,40 @@ SS_RAY_KERNEL void shadow_kernel(TileK T, float* __restrict__ out,
   }
 }
 
+// The forward (s alone) of small tiles: the four wavefronts of a workgroup share one
+// 8 x 8 ray tile and take every fourth of its runs each; the smallest clearance is
+// found in LDS.  A run's chain of dependent gathers, one per level, is what a launch
+// that leaves the SIMDs a wavefront or two each waits for, and the runs of a ray do
+// not depend on each other: only the early exits do, and a run another wavefront
+// would have skipped cannot change s.  The launcher's rule says where it pays.
+#define SS_SPLIT 4
+
+template <bool SPHERE, int MODE>
+SS_RAY_KERNEL void shadow_split_kernel(TileK T, float* __restrict__ out, int nbx) {
+  __shared__ float key[SS_SPLIT][64];
+  const int lane = threadIdx.x & 63;
+  const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int li = ((int)blockIdx.x % nbx) * 8 + (lane & 7);
+  const int lj = ((int)blockIdx.x / nbx) * 8 + (lane >> 3);
+  const bool in = li < T.RW && lj < T.RH;
+  float best = SS_INF;
+  if (in) {
+    const int i = T.rx0 + li, j = T.ry0 + lj;
+    Ray<SPHERE> r;
+    ray_init(T, i, j, T.h[j * T.W + i], r);
+    unsigned n_lb = 0, n_smp = 0;
+    best = shadow_dp<SPHERE, MODE == SS_MODE_POINT>(T, r, terrain_top(T, r), n_lb, n_smp, part,
+                                                    SS_SPLIT).key;
+  }
+  key[part][lane] = best;
+  __syncthreads();
+  if (part == 0 && in) {
+#pragma unroll
+    for (int k = 1; k < SS_SPLIT; ++k) best = fminf(best, key[k][lane]);
+    out[lj * T.RW + li] = disc_fraction(angle_of(best), T);
+  }
+}
+
 // Adjoint: recompute the forward decisions (or read the deciding sample the
 // forward recorded, SAVED), then apply the chain rule through that sample.  With the decisions fixed, s depends on the origin
 // height (through rho and the texture path), the four bilinear taps, and the
@@ -618,6 +652,28 @@ void grid_for(const TileK& T, int ray_tile, int* nbx, int* nblocks) {
   *nblocks = bx * by;
 }
 
+// Whether a forward launch of nb 256-ray blocks takes the split form: descents, s
+// alone, the default ray tile, and at most 2.5 wavefronts per SIMD otherwise
+// (T.wg_group / 2 SIMDs on the device).  us per launch, whole / split, on square
+// tiles: 96: 13.4 / 7.1, 256: 19.0 / 11.8, 320: 21.1 / 13.4, 384 (2.3 wavefronts):
+// 22.0 / 18.4, 448 (3.1): 23.9 / 24.1, 512: 27.6 / 31.0; point samples 256: 10.7 / 7.1,
+// 384: 14.0 / 12.2, 448: 16.3 / 15.7, 512: 17.2 / 18.9.
+static bool split_pays(const TileK& T, int mode, int flags, int ray_tile, int nb) {
+  return (mode == SS_MODE_DP || mode == SS_MODE_POINT) && flags == FWD_PLAIN &&
+         ray_tile == SS_TILE_8x8 && T.nseg > 1 && 8LL * nb <= 5LL * (T.wg_group / 2);
+}
+
+template <bool SPHERE>
+static hipError_t launch_split(const TileK& T, int mode, float* out, hipStream_t stream) {
+  const int nbx = (T.RW + 7) / 8, nby = (T.RH + 7) / 8;
+  const dim3 grid((unsigned)(nbx * nby)), block(64 * SS_SPLIT);
+  if (mode == SS_MODE_POINT)
+    hipLaunchKernelGGL((shadow_split_kernel<SPHERE, SS_MODE_POINT>), grid, block, 0, stream, T, out, nbx);
+  else
+    hipLaunchKernelGGL((shadow_split_kernel<SPHERE, SS_MODE_DP>), grid, block, 0, stream, T, out, nbx);
+  return hipGetLastError();
+}
+
 template <bool SPHERE, int TW, int MODE>
 static void launch_fwd_m(const TileK& T, int flags, float* out, unsigned long long* counter,
                          int* sample, int nbx, int nb, hipStream_t stream) {
@@ -664,6 +720,12 @@ hipError_t launch_forward(const TileK& T, bool sphere, int mode, int ray_tile, b
                           float* out, unsigned long long* counter, int* sample,
                           hipStream_t stream) {
   const int flags = count ? FWD_COUNT : (sample ? FWD_SAVE : FWD_PLAIN);
+  int nbx, nb;
+  grid_for(T, ray_tile, &nbx, &nb);
+  if (nb == 0) return hipSuccess;
+  if (split_pays(T, mode, flags, ray_tile, nb))
+    return sphere ? launch_split<true>(T, mode, out, stream)
+                  : launch_split<false>(T, mode, out, stream);
   return sphere ? launch_fwd_s<true>(T, mode, ray_tile, flags, out, counter, sample, stream)
                 : launch_fwd_s<false>(T, mode, ray_tile, flags, out, counter, sample, stream);
 }

@@ -5,7 +5,8 @@ exact bounds where two are close, runs ended once nothing below can matter); oth
 take the general descent.  Shading the same texel centres in a shuffled order puts
 rays of different headings, runs and terrain into one wavefront, so the two launches
 choose differently among those paths; every value has to be the same, bit for bit,
-as has every value with the early exits off."""
+as has every value with the early exits off, and with another ray tile (small tiles
+in the default one share a ray tile's runs among the wavefronts of a workgroup)."""
 import math
 
 import numpy as np
@@ -63,15 +64,19 @@ def test_any_wavefront_same_value(ss, shape):
         print(shape, deg, az, radius, texel, flush=True)
         h = torch.from_numpy(rough(*shape, seed=k, amp=15.0 * texel)).cuda()
         e = math.radians(deg)
-        for mode in (ss.SS_MODE_DP, ss.SS_MODE_EXACT):
+        for mode in (ss.SS_MODE_DP, ss.SS_MODE_POINT, ss.SS_MODE_EXACT):
             p = ss.Params(radius_m=radius, max_len_m=0.0 if k % 2 else 300.0 * texel, mode=mode)
             grid = ss.shadow_cast(h, texel, e, az, RL, p)
             p.prune = 0
             full = ss.shadow_cast(h, texel, e, az, RL, p)
             p.prune = 1
+            p.ray_tile = ss.RAY_TILES["16x4"]
+            other = ss.shadow_cast(h, texel, e, az, RL, p)
+            p.ray_tile = 0
             mixed = shuffled(ss, h, texel, e, az, p, 7 + k)
             assert torch.equal(grid, full), (deg, mode)
             assert torch.equal(grid, mixed), (deg, mode)
+            assert torch.equal(grid, other), (deg, mode)
 
 
 def test_holes_and_infinities(ss):
