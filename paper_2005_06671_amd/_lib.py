@@ -131,6 +131,8 @@ class SoftShadowError(RuntimeError):
 def lib() -> C.CDLL:
     """The loaded HIP library; raises if it has not been built (no fallback)."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             how = ("build it with `python -c 'import __graft_entry__ as g; g.build()'` or "

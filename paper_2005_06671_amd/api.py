@@ -8,6 +8,7 @@ from __future__ import annotations
 import ctypes as C
 import math
 from dataclasses import dataclass
+from functools import lru_cache
 
 import torch
 
@@ -17,6 +18,10 @@ SUN_RADIUS_RAD = math.radians(0.267)
 
 
 def _stream(device=None) -> int:
+    """The current stream's handle (without the Stream object around it where the device is
+    given: 3 us of a call's host time)."""
+    if device is not None and device.index is not None:
+        return torch._C._cuda_getCurrentRawStream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
 
 
@@ -49,16 +54,42 @@ class Params:
                           float(self.uniform_step), int(self.prune), int(self.ray_tile), lst)
 
 
+# The layout depends on the sizes alone, so each is asked of the library once.
+@lru_cache(maxsize=1024)
 def maxmip_levels(width: int, rows: int) -> int:
     return L.lib().ss_maxmip_levels(width, rows)
 
 
+@lru_cache(maxsize=1024)
 def maxmip_floats(width: int, rows: int) -> int:
     return L.lib().ss_maxmip_floats(width, rows)
 
 
+@lru_cache(maxsize=4096)
 def maxmip_level_offset(width: int, rows: int, level: int) -> int:
     return L.lib().ss_maxmip_level_offset(width, rows, level)
+
+
+@lru_cache(maxsize=256)
+def _level_pieces(width: int, rows: int) -> tuple:
+    """Sizes that cut a packed mipmap into its levels and the padding after each, and the
+    levels' shapes: ([floats, padding, ...], [(rows_m, width_m), ...])."""
+    sizes, shapes = [], []
+    w, r = width, rows
+    for m in range(1, maxmip_levels(width, rows)):
+        w, r = (w + 1) // 2, (r + 1) // 2
+        here = maxmip_level_offset(width, rows, m)
+        sizes += [w * r, maxmip_level_offset(width, rows, m + 1) - here - w * r]
+        shapes.append((r, w))
+    return sizes, shapes
+
+
+def _unpack(mm: torch.Tensor, width: int, rows: int) -> list:
+    sizes, shapes = _level_pieces(width, rows)
+    if not shapes:
+        return []
+    pieces = mm[:maxmip_floats(width, rows)].split(sizes)
+    return [p.view(s) for p, s in zip(pieces[::2], shapes)]
 
 
 def maxmip(h: torch.Tensor, fuse_depth: int = 0, out: torch.Tensor | None = None) -> torch.Tensor:
@@ -77,19 +108,15 @@ def maxmip(h: torch.Tensor, fuse_depth: int = 0, out: torch.Tensor | None = None
 
 def maxmip_unpack(mm: torch.Tensor, width: int, rows: int) -> list:
     """Views of levels 1..L-1 of a packed mipmap as [rows_m, width_m] tensors."""
-    out = []
-    w, r = width, rows
-    for m in range(1, maxmip_levels(width, rows)):
-        w, r = (w + 1) // 2, (r + 1) // 2
-        off = maxmip_level_offset(width, rows, m)
-        out.append(mm[off:off + w * r].view(r, w))
-    return out
+    return _unpack(mm, width, rows)
 
 
+@lru_cache(maxsize=1024)
 def bound_floats(width: int, rows: int) -> int:
     return L.lib().ss_bound_floats(width, rows)
 
 
+@lru_cache(maxsize=4096)
 def bound_level_offset(width: int, rows: int, level: int) -> int:
     return L.lib().ss_bound_level_offset(width, rows, level)
 
@@ -111,11 +138,8 @@ def bound_build(h: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tenso
 def bound_unpack(b: torch.Tensor, width: int, rows: int) -> list:
     """Views of levels 0..L-1 of a packed tap-bound pyramid as [rows_m, width_m] tensors."""
     out = [b[:width * rows].view(rows, width)]
-    w, r = width, rows
-    for m in range(1, maxmip_levels(width, rows)):
-        w, r = (w + 1) // 2, (r + 1) // 2
-        off = bound_level_offset(width, rows, m)
-        out.append(b[off:off + w * r].view(r, w))
+    if maxmip_levels(width, rows) > 1:
+        out += _unpack(b[bound_level_offset(width, rows, 1):], width, rows)
     return out
 
 
@@ -165,7 +189,8 @@ def shadow_cast(h: torch.Tensor, texel_m: float, elev: float, azim: float,
     bound = _bound_for(h, params, bound)
     if out is None:
         out = torch.empty(_ray_shape(h, window), dtype=torch.float32, device=h.device)
-    _check_ray_buf(out, h, window, torch.float32, "out")
+    else:
+        _check_ray_buf(out, h, window, torch.float32, "out")
     t = _tile(h, mm, texel_m, bound, window)
     s = _sun(elev, azim, ang_radius)
     p = params.c()
@@ -507,6 +532,16 @@ def probe_gather(src: torch.Tensor, window: int = 0, iters: int = 64, n_threads:
     return out
 
 
+def _sun_grads(gsun: torch.Tensor, elev, azim) -> tuple:
+    """dL/delev and dL/dazim on their tensors' devices: one copy (and, to the host, one wait)
+    where both live on the same one."""
+    devs = [v.device if isinstance(v, torch.Tensor) else None for v in (elev, azim)]
+    if devs[0] == devs[1] and devs[0] is not None:
+        g = gsun.to(devs[0])
+        return g[0], g[1]
+    return tuple(gsun[k].to(d) if d is not None else None for k, d in enumerate(devs))
+
+
 class ShadowCast(torch.autograd.Function):
     """s = shadow(h, elev, azim) with the hand-written adjoint kernel as backward.
 
@@ -554,8 +589,7 @@ class ShadowCast(torch.autograd.Function):
         else:
             gh, gsun = shadow_cast_backward_penumbra(hd, texel_m, e, a, sample, g, ang_radius,
                                                      params, mm=mm, bound=bound, window=window)
-        ge = gsun[0].to(elev.device) if isinstance(elev, torch.Tensor) else None
-        ga = gsun[1].to(azim.device) if isinstance(azim, torch.Tensor) else None
+        ge, ga = _sun_grads(gsun, elev, azim)
         return gh, ge, ga, None, None, None, None, None
 
 
@@ -638,8 +672,7 @@ class ShadowPoints(torch.autograd.Function):
         g = torch.nan_to_num(grad_s.contiguous(), nan=0.0)
         gh, gsun = shadow_points_backward(hd, texel_m, e, a, xy, g, ang_radius, params, mm=mm,
                                           bound=bound if ctx.has_bound else None)
-        ge = gsun[0].to(elev.device) if isinstance(elev, torch.Tensor) else None
-        ga = gsun[1].to(azim.device) if isinstance(azim, torch.Tensor) else None
+        ge, ga = _sun_grads(gsun, elev, azim)
         return gh, ge, ga, None, None, None, None
 
 
