@@ -119,6 +119,9 @@ struct ResampleK {
   double R;
   double cd[3], exd[3], eyd[3], oxd, oyd, Dd;  // destination frame
   double cs[3], exs[3], eys[3], oxs, oys, Ds;  // source frame
+  // set by launch_resample: 1 / Ds and the destination texels to visit
+  double invDs;
+  int i0, i1, j0, j1;
 };
 hipError_t launch_resample(const ResampleK& K, hipStream_t stream);
 
