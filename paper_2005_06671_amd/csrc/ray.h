@@ -532,7 +532,9 @@ __device__ __forceinline__ void pick_piece(const TileK& T, const Ray<SPHERE>& r,
     const bool s2 = lb2 <= b01;
     t1 = lanes(s1);
     t2 = lanes(s2);
-    found = lanes((s2 ? lb2 : b01) < SS_INF);
+    // (below +inf; written so because a ballot of `< inf` comes out as "not equal to
+    // inf", which a missing height passes)
+    found = lanes((s2 ? lb2 : b01) <= 3.402823466e38f);
     n0 = s2 ? c2 : (s1 ? c1 : st.u0);
     n1 = s2 ? st.u1 : (s1 ? c2 : c1);
   };

@@ -99,3 +99,24 @@ def test_holes_and_infinities(ss):
         assert torch.equal(grid[~bad], mixed[~bad]), (deg, az)
         p.prune = 0
         assert torch.equal(grid, ss.shadow_cast(h, 20.0, math.radians(deg), az, RL, p)), (deg, az)
+
+
+@pytest.mark.parametrize("rows,width,share", [(257, 300, 0.05), (700, 900, 0.003)])
+def test_scattered_missing_heights(ss, rows, width, share):
+    """Single missing heights show at the lowest level only, where a run whose first texel
+    has none ends: grid launches (wavefronts that descend together) agree with shuffled
+    points, on the sphere and on the plane."""
+    g = torch.Generator().manual_seed(1)
+    h = torch.from_numpy(rough(rows, width, 1))
+    h[torch.rand(rows, width, generator=g) < share] = math.nan
+    h = h.cuda()
+    bad = torch.isnan(h)
+    bad[:, :-1] |= torch.isnan(h)[:, 1:]
+    bad[:-1] |= bad[1:].clone()
+    for deg, az in ((1.5, 0.7), (4.0, 3.9), (0.2, 2.0)):
+        for radius in (MOON, math.inf):
+            print("scattered", rows, width, deg, radius, flush=True)
+            p = ss.Params(radius_m=radius)
+            grid = ss.shadow_cast(h, 20.0, math.radians(deg), az, RL, p)
+            mixed = shuffled(ss, h, 20.0, math.radians(deg), az, p, 5)
+            assert torch.equal(grid[~bad], mixed[~bad]), (deg, az, radius)
