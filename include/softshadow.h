@@ -123,6 +123,9 @@ int64_t ss_maxmip_floats(int32_t width, int32_t rows);
 /* Builds levels >= 1: each texel is the maximum of the (up to four) texels it
  * covers one level down; texels beyond a ragged edge are absent; -0 is stored
  * as +0.  Bit-exact.  fuse_depth = levels written per launch (1..6, 0 = tuned).
+ * The float after the top texel (inside the total size) records whether every
+ * height is finite: stepping passes over terrain only where that is known, so a
+ * mipmap that was not built here is correct to use but slower to step through.
  * width or rows == 0 is an empty no-op. */
 int32_t ss_maxmip_build(const float* d_height, int32_t width, int32_t rows, float* d_maxmip,
                         int32_t fuse_depth, void* stream);

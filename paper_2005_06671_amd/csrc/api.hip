@@ -95,7 +95,14 @@ static int32_t maxmip_build(const float* d_height, int32_t W, int32_t H, float* 
       off[k] = (int)ss_maxmip_level_offset(W, H, src_m + 1 + k);
       dims_of(W, H, src_m + 1 + k, &w[k], &h[k]);
     }
-    SS_HIP(launch_maxmip(src, sw, sh, d_mm, off, w, h, F, stream));
+    int bw = 0, bh = 0;
+    const float* below = nullptr;
+    if (src_m > 0) {
+      dims_of(W, H, src_m - 1, &bw, &bh);
+      below = src_m == 1 ? d_height : d_mm + ss_maxmip_level_offset(W, H, src_m - 1);
+    }
+    SS_HIP(launch_maxmip(src, sw, sh, d_mm, off, w, h, F, below, bw, bh, src_m + F == L - 1,
+                         finite_key(W, H), stream));
     src_m += F;
   }
   return SS_OK;
@@ -263,6 +270,7 @@ static int32_t make_tilek(const ss_tile* t, const ss_sun* s, const Resolved& rp,
   K->tan_margin = (float)tan(1e-5);
   K->prune = rp.prune;
   K->ustep = (float)(rp.uniform_step * delta);
+  K->ulev = chunk_level(rp.uniform_step);
 
   // concatenated runs: run j traces N'_j levels (top level N'_j - 1) and
   // covers 2^(N'_j - 1) texels of travel; enough runs to reach the cap, or

@@ -12,7 +12,7 @@
 #define SS_MAXLEV 18   // supports max(width, rows) <= 65536
 #define SS_MAXSEG 48   // concatenated runs per ray
 #define SS_TILEK_BYTES 928
-#define SS_FITRUNS 30          // runs with bounds of the tip height's fit
+#define SS_FITRUNS 29          // runs with bounds of the tip height's fit
 #define SS_REFIT 3             // the fit is taken again this many levels below a run's top
 #define SS_REFIT_FROM 7        // in runs of this level and up
 #define SS_FIT_NONE 0xffffffffu  // no fit: the run takes the general descent
@@ -49,12 +49,36 @@ struct TileK {
   int prune;                 // 1: result-invariant early exits enabled
   int wg_group;              // per-tile kernels: workgroup ids are remapped within groups of
                              // this many (one device-full, a multiple of 8)
+  int ulev;                  // uniform stepping: mip level whose texels hold a chunk's path (chunk_level)
   unsigned fit_err[SS_FITRUNS];  // run j: error bounds of the tip height's fits (fit_err_pack)
 };
 // The batched workspace holds one block per (tile, sun) pair, and how many
 // pairs the fixed array of the allocation-free call takes follows from this
 // size: callers rely on which batches fit.
 static_assert(sizeof(TileK) == SS_TILEK_BYTES, "the parameter block's size is part of the interface");
+
+// The word after the mipmap's top texel: finite_word(top, key) when every height of
+// the tile is a finite number (any other value: not known to be).  The tile's size
+// and top are in it so that a word left by another tile in the same memory does not
+// pass for it.
+__host__ __device__ inline unsigned finite_key(int W, int H) {
+  return 0x5f3c9a17u ^ ((unsigned)W * 0x9e3779b1u) ^ ((unsigned)H * 0x85ebca6bu);
+}
+__device__ __forceinline__ unsigned finite_word(float top, unsigned key) {
+  return __float_as_uint(top) ^ key;
+}
+
+// Uniform stepping looks at SS_CHUNK steps at a time, and at four such chunks.
+#define SS_CHUNK 16
+
+// The finest mip level of whose texels two by two hold the taps of a chunk of
+// `step` texels per step: one texel there spans the chunk's travel (a tenth to
+// spare for tiles whose plane bends away) and the taps around its ends.
+inline int chunk_level(double step) {
+  int m = 0;
+  while (ldexp(1.0, m) < (SS_CHUNK - 1) * step * 1.1 + 2.0) ++m;
+  return m;
+}
 
 // Run j starts at half-texel grid index a0 (tau_j = (a0 + 1) delta/2) and
 // descends from mip level m0.  a0 stays below 2^27: at most SS_MAXSEG runs of

@@ -9,9 +9,12 @@ namespace ss {
 #define SS_ITEM_BLOCKS 1  // ray blocks (256 rays each) per queue item of the batched kernel
 #define SS_NXCD 8         // XCDs; workgroup ids are dealt round-robin over them
 
-// Maximum mipmap: levels [m_src+1, m_src+F] from level m_src (F <= 6).
+// Maximum mipmap: levels [m_src+1, m_src+F] from level m_src (F <= 6).  below: level
+// m_src - 1 (bw x bh; nullptr when m_src is 0); last: the top is among them; key:
+// finite_key of the tile.
 hipError_t launch_maxmip(const float* src, int sw, int sh, float* dst_base, const int* dst_off,
-                         const int* dst_w, const int* dst_h, int F, hipStream_t stream);
+                         const int* dst_w, const int* dst_h, int F, const float* below, int bw,
+                         int bh, int last, unsigned key, hipStream_t stream);
 
 // Tap-bound pyramid level 0: maximum over each texel's 3 x 3 block (clipped).
 hipError_t launch_block3_max(const float* src, int W, int H, float* dst, hipStream_t stream);

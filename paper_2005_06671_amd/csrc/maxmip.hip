@@ -7,6 +7,15 @@
 //   +3, +4  by cross-lane max within the wavefront (no LDS),
 //   +5, +6  through a 4 x 4 LDS tile.
 // Every texel is read from HBM once per launch; levels are written once.
+//
+// The build also says whether every height is a finite number, which the levels do
+// not show (a maximum passes over a missing height): in the word after the top texel,
+// inside the top level's 64-float slot (finite_word).  A launch hands its part of the
+// answer to the next as NaN texels in the last level it writes; the workgroup that
+// reads such a texel puts its maximum back from the level below.  No other workgroup
+// reads it, so this takes no further launch, memory or pass: 16 multiply-adds a thread,
+// and a barrier where fewer than five levels are written (a 4096^2 tile's first launch
+// 16.5 us before and 17.2 with it; both launches of a 256^2 tile 5.8 and 6.4).
 #include "kernels.h"
 
 namespace ss {
@@ -15,15 +24,19 @@ struct MipDst {
   int off[6];
   int w[6];
   int h[6];
+  const float* below;  // the level under the source (nullptr: the source is level 0)
+  int bw, bh;
+  int last;            // the last level written is the top
+  unsigned key;        // finite_key of the tile
 };
 
 __device__ __forceinline__ float canon(float v) { return v + 0.0f; }  // -0 -> +0
 
 template <int F>
-__global__ __launch_bounds__(256) void maxmip_kernel(const float* __restrict__ src, int sw, int sh,
-                                                     float* __restrict__ dst, MipDst d, int nbx,
-                                                     int vec_ok) {
+__global__ __launch_bounds__(256) void maxmip_kernel(const float* src, int sw, int sh, float* dst,
+                                                     MipDst d, int nbx, int vec_ok) {
   __shared__ float lds[4][4];
+  __shared__ int lds_bad[4];  // per wavefront
   const int b = blockIdx.x;
   const int bx = b % nbx, by = b / nbx;
   const int t = threadIdx.x;
@@ -31,21 +44,61 @@ __global__ __launch_bounds__(256) void maxmip_kernel(const float* __restrict__ s
   const int col0 = bx * 64 + c4 * 4, row0 = by * 64 + rg * 4;
   const float NEG = -__builtin_inff();
   float v[4][4];
+  float zero[4];  // 0 times finite numbers adds up to 0, anything else to NaN
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int row = row0 + r;
+    zero[r] = 0.0f;
     if (row < sh && vec_ok && col0 + 3 < sw) {
       const float4 q = *reinterpret_cast<const float4*>(src + (size_t)row * sw + col0);
       v[r][0] = canon(q.x);
       v[r][1] = canon(q.y);
       v[r][2] = canon(q.z);
       v[r][3] = canon(q.w);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) zero[r] = fmaf(v[r][c], 0.0f, zero[r]);
     } else {
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        v[r][c] = (row < sh && col0 + c < sw) ? canon(src[(size_t)row * sw + col0 + c]) : NEG;
+      for (int c = 0; c < 4; ++c) {
+        v[r][c] = NEG;
+        if (row < sh && col0 + c < sw) {
+          v[r][c] = canon(src[(size_t)row * sw + col0 + c]);
+          zero[r] = fmaf(v[r][c], 0.0f, zero[r]);
+        }
+      }
     }
   }
+  const bool mine = !((zero[0] + zero[1]) + (zero[2] + zero[3]) == 0.0f);
+  if (mine && d.below) {
+    for (int k = 0; k < 16; ++k) {
+      const int y = row0 + (k >> 2), x = col0 + (k & 3);
+      if (y < sh && x < sw && __builtin_isnan(v[k >> 2][k & 3])) {
+        const bool hx = 2 * x + 1 < d.bw, hy = 2 * y + 1 < d.bh;  // absent beyond the edge
+        const float* p = d.below + (size_t)(2 * y) * d.bw + 2 * x;
+        const float m = fmaxf(fmaxf(canon(p[0]), hx ? canon(p[1]) : NEG),
+                              fmaxf(hy ? canon(p[d.bw]) : NEG, hx && hy ? canon(p[d.bw + 1]) : NEG));
+        const_cast<float*>(src)[(size_t)y * sw + x] = m;
+        v[k >> 2][k & 3] = m;
+      }
+    }
+  }
+  const bool wave_bad = __any(mine);
+  if ((t & 63) == 0) lds_bad[t >> 6] = wave_bad;
+  // for the last level written, after a barrier: NaN hands the answer on, and the
+  // thread that writes the top's texel leaves it beside it
+  float mark = 0.0f;
+  bool bad = false;
+  auto gather = [&] {
+    __syncthreads();
+    bad = (lds_bad[0] | lds_bad[1] | lds_bad[2] | lds_bad[3]) != 0;
+    mark = bad && !d.last ? __builtin_nanf("") : 0.0f;
+  };
+  auto verdict = [&](float top) {
+    if (d.last)
+      reinterpret_cast<unsigned*>(dst)[d.off[F - 1] + 1] = bad ? ~finite_word(top, d.key)
+                                                               : finite_word(top, d.key);
+  };
+  if (F < 5) gather();
   // level +1: 2 x 2 per thread
   float a[2][2];
 #pragma unroll
@@ -53,7 +106,8 @@ __global__ __launch_bounds__(256) void maxmip_kernel(const float* __restrict__ s
 #pragma unroll
     for (int c = 0; c < 2; ++c)
       a[r][c] = fmaxf(fmaxf(v[2 * r][2 * c], v[2 * r][2 * c + 1]),
-                      fmaxf(v[2 * r + 1][2 * c], v[2 * r + 1][2 * c + 1]));
+                      fmaxf(v[2 * r + 1][2 * c], v[2 * r + 1][2 * c + 1])) +
+                (F == 1 ? mark : 0.0f);
   {
     const int w1 = d.w[0], h1 = d.h[0];
     float* L1 = dst + d.off[0];
@@ -71,38 +125,51 @@ __global__ __launch_bounds__(256) void maxmip_kernel(const float* __restrict__ s
       }
     }
   }
-  if (F == 1) return;
+  if (F == 1) {
+    if (t == 0) verdict(a[0][0]);
+    return;
+  }
   // level +2: one value per thread
   float b2 = fmaxf(fmaxf(a[0][0], a[0][1]), fmaxf(a[1][0], a[1][1]));
   {
     const int rr = by * 16 + rg, cc = bx * 16 + c4;
-    if (rr < d.h[1] && cc < d.w[1]) dst[d.off[1] + (size_t)rr * d.w[1] + cc] = b2;
+    if (rr < d.h[1] && cc < d.w[1]) dst[d.off[1] + (size_t)rr * d.w[1] + cc] = b2 + (F == 2 ? mark : 0.0f);
   }
-  if (F == 2) return;
+  if (F == 2) {
+    if (t == 0) verdict(b2);
+    return;
+  }
   // level +3: lanes (c4, c4^1) x (rg, rg^1) of the same wavefront
   float b3 = fmaxf(b2, __shfl_xor(b2, 1, 64));
   b3 = fmaxf(b3, __shfl_xor(b3, 16, 64));
   if (((c4 | rg) & 1) == 0) {
     const int rr = by * 8 + (rg >> 1), cc = bx * 8 + (c4 >> 1);
-    if (rr < d.h[2] && cc < d.w[2]) dst[d.off[2] + (size_t)rr * d.w[2] + cc] = b3;
+    if (rr < d.h[2] && cc < d.w[2]) dst[d.off[2] + (size_t)rr * d.w[2] + cc] = b3 + (F == 3 ? mark : 0.0f);
   }
-  if (F == 3) return;
+  if (F == 3) {
+    if (t == 0) verdict(b3);
+    return;
+  }
   // level +4: lanes (c4, c4^2) x (rg, rg^2)
   float b4 = fmaxf(b3, __shfl_xor(b3, 2, 64));
   b4 = fmaxf(b4, __shfl_xor(b4, 32, 64));
   if (((c4 | rg) & 3) == 0) {
     const int rr = by * 4 + (rg >> 2), cc = bx * 4 + (c4 >> 2);
-    if (rr < d.h[3] && cc < d.w[3]) dst[d.off[3] + (size_t)rr * d.w[3] + cc] = b4;
+    if (rr < d.h[3] && cc < d.w[3]) dst[d.off[3] + (size_t)rr * d.w[3] + cc] = b4 + (F == 4 ? mark : 0.0f);
     lds[rg >> 2][c4 >> 2] = b4;
   }
-  if (F == 4) return;
-  __syncthreads();
+  if (F == 4) {
+    if (t == 0) verdict(b4);
+    return;
+  }
+  gather();
   if (t < 4) {
     const int r5 = t >> 1, c5 = t & 1;
     const float m5 = fmaxf(fmaxf(lds[2 * r5][2 * c5], lds[2 * r5][2 * c5 + 1]),
                            fmaxf(lds[2 * r5 + 1][2 * c5], lds[2 * r5 + 1][2 * c5 + 1]));
     const int rr = by * 2 + r5, cc = bx * 2 + c5;
-    if (rr < d.h[4] && cc < d.w[4]) dst[d.off[4] + (size_t)rr * d.w[4] + cc] = m5;
+    if (rr < d.h[4] && cc < d.w[4]) dst[d.off[4] + (size_t)rr * d.w[4] + cc] = m5 + (F == 5 ? mark : 0.0f);
+    if (F == 5 && t == 0) verdict(m5);
   }
   if (F == 5) return;
   if (t == 0) {
@@ -111,7 +178,8 @@ __global__ __launch_bounds__(256) void maxmip_kernel(const float* __restrict__ s
     for (int r = 0; r < 4; ++r)
 #pragma unroll
       for (int c = 0; c < 4; ++c) m6 = fmaxf(m6, lds[r][c]);
-    if (by < d.h[5] && bx < d.w[5]) dst[d.off[5] + (size_t)by * d.w[5] + bx] = m6;
+    if (by < d.h[5] && bx < d.w[5]) dst[d.off[5] + (size_t)by * d.w[5] + bx] = m6 + mark;
+    verdict(m6);
   }
 }
 
@@ -149,8 +217,14 @@ hipError_t launch_block3_max(const float* src, int W, int H, float* dst, hipStre
 }
 
 hipError_t launch_maxmip(const float* src, int sw, int sh, float* dst_base, const int* dst_off,
-                         const int* dst_w, const int* dst_h, int F, hipStream_t stream) {
+                         const int* dst_w, const int* dst_h, int F, const float* below, int bw,
+                         int bh, int last, unsigned key, hipStream_t stream) {
   MipDst d;
+  d.below = below;
+  d.bw = bw;
+  d.bh = bh;
+  d.last = last;
+  d.key = key;
   for (int k = 0; k < 6; ++k) {
     d.off[k] = k < F ? dst_off[k] : 0;
     d.w[k] = k < F ? dst_w[k] : 0;
