@@ -354,6 +354,13 @@ __device__ __forceinline__ float need_tangent(const TileK& T, float key) {
   return (k + T.tan_margin) * ss_rcp(1.0f - k * T.tan_margin);
 }
 
+// tan(alpha + margin) for the tangent key of alpha: samples that clear it cannot take
+// the deciding sample's place, where those that clear need_tangent's may on a lit ray.
+__device__ __forceinline__ float keep_tangent(const TileK& T, float key) {
+  const float k = fmaxf(key, -1e30f);
+  return k * T.tan_margin < 0.5f ? (k + T.tan_margin) * ss_rcp(1.0f - k * T.tan_margin) : SS_INF;
+}
+
 // The smallest of a run's final samples by height above the terrain (Alg. 1,
 // final level), as `<=` scanning from the near end.
 struct Deepest {
@@ -973,8 +980,9 @@ __device__ __forceinline__ float angle_of(float key) {
 
 // Smallest clearance over the concatenated runs (Sec. 3.3), each by the
 // texel descent (POINT = false) or Alg. 1's point samples (POINT = true): over runs
-// j0, j0 + stride, ...
-template <bool SPHERE, bool POINT = false>
+// j0, j0 + stride, ...  KEEP: the deciding sample itself counts as a result, not only
+// its clearance up to r_L, so a run ends early only where it cannot hold that sample.
+template <bool SPHERE, bool POINT = false, bool KEEP = false>
 __device__ __forceinline__ RayResult shadow_dp(const TileK& T, const Ray<SPHERE>& r, float top,
                                                unsigned& n_lb, unsigned& n_smp, int j0 = 0,
                                                int stride = 1) {
@@ -999,7 +1007,7 @@ __device__ __forceinline__ RayResult shadow_dp(const TileK& T, const Ray<SPHERE>
     if (POINT)
       point_run(T, r, j, so, n_lb, n_smp);
     else
-      descend_run(T, r, way, j, need, so, n_lb, n_smp);
+      descend_run(T, r, way, j, KEEP ? keep_tangent(T, best) : need, so, n_lb, n_smp);
     if (so.valid && so.key < best) {
       best = so.key;
       res.t = so.t;
@@ -1058,9 +1066,10 @@ __device__ __forceinline__ bool steps_clear(const TileK& T, const Ray<SPHERE>& r
 // Bound by instruction issue (53 a step in such a chunk, 65 with the clamps and four
 // gathers): a 1024^2 tile at 1.5 deg, half-texel steps to 30 km, 764 us step by step,
 // 600 in chunks and 285 with the passing over, which looks at terrain maxima once
-// for 16 or 64 steps where most steps lie far above the terrain.  64 first: of a lit
-// ray's steps most can go at once; 256 holds too high a maximum to show it.
-template <bool SPHERE>
+// for 16 or 64 steps where most steps lie far above the terrain.
+//
+// KEEP: as in shadow_dp; every step before an exit is taken.
+template <bool SPHERE, bool KEEP>
 __device__ __forceinline__ RayResult shadow_uniform(const TileK& T, const Ray<SPHERE>& r, float top,
                                                     unsigned& n_smp) {
   RayResult res;
@@ -1085,7 +1094,7 @@ __device__ __forceinline__ RayResult shadow_uniform(const TileK& T, const Ray<SP
   const Level L0 = level_of(T, 0);
   const int base = __mul24(r.j, L0.w) + r.i;
   const int ma = min(T.ulev, T.L - 1), mb = min(T.ulev + 2, T.L - 1);
-  const bool skip = T.prune && heights_finite(T);
+  const bool skip = !KEEP && T.prune && heights_finite(T);
   const bool wide = skip && T.lev[mb].w >= 2 && T.lev[mb].h >= 2;
   const bool small = skip && T.lev[ma].w >= 2 && T.lev[ma].h >= 2;
   bool done = false;
@@ -1184,7 +1193,7 @@ __device__ __forceinline__ float bound_at(const TileK& T, const int* tab, int m,
 // runs first and its deciding sample, a sample of the same grid computed by
 // the same arithmetic, seeds the minimum when it lies within the cap.  A ray
 // the descent already finds in umbra is then done.
-template <bool SPHERE>
+template <bool SPHERE, bool KEEP>
 __device__ __forceinline__ RayResult shadow_exact(const TileK& T, const Ray<SPHERE>& r, float top,
                                                   unsigned& n_tst, unsigned& n_smp,
                                                   const int* tab) {
@@ -1196,7 +1205,7 @@ __device__ __forceinline__ RayResult shadow_exact(const TileK& T, const Ray<SPHE
   float best = SS_INF;
   if (T.prune) {
     unsigned n_lb = 0, n_dp = 0;
-    const RayResult d = shadow_dp(T, r, top, n_lb, n_dp);
+    const RayResult d = shadow_dp<SPHERE, false, KEEP>(T, r, top, n_lb, n_dp);
     n_tst += n_lb;
     n_smp += n_dp;
     if (d.valid && d.t <= T.ucap) {
@@ -1275,13 +1284,14 @@ __device__ __forceinline__ float terrain_top(const TileK& T, const Ray<SPHERE>& 
   return r.dz > t0 ? r.dz : t0;
 }
 
-// The shadow clearance of one ray by the chosen method.
-template <bool SPHERE, int MODE>
+// The shadow clearance of one ray by the chosen method.  KEEP: for a caller that hands
+// out the deciding sample.
+template <bool SPHERE, int MODE, bool KEEP = false>
 __device__ __forceinline__ RayResult trace_ray(const TileK& T, const Ray<SPHERE>& r, unsigned& n_lb,
                                                unsigned& n_smp, const int* tab) {
   const float top = terrain_top(T, r);
-  if (MODE == SS_MODE_EXACT) return shadow_exact(T, r, top, n_lb, n_smp, tab);
+  if (MODE == SS_MODE_EXACT) return shadow_exact<SPHERE, KEEP>(T, r, top, n_lb, n_smp, tab);
   if (MODE == SS_MODE_POINT) return shadow_dp<SPHERE, true>(T, r, top, n_lb, n_smp);
-  if (MODE == SS_MODE_UNIFORM) return shadow_uniform(T, r, top, n_smp);
-  return shadow_dp<SPHERE, false>(T, r, top, n_lb, n_smp);
+  if (MODE == SS_MODE_UNIFORM) return shadow_uniform<SPHERE, KEEP>(T, r, top, n_smp);
+  return shadow_dp<SPHERE, false, KEEP>(T, r, top, n_lb, n_smp);
 }

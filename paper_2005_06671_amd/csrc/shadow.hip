@@ -66,7 +66,7 @@ SS_RAY_KERNEL void shadow_kernel(TileK T, float* __restrict__ out,
     const float hp = T.h[j * T.W + i];
     Ray<SPHERE> r;
     ray_init(T, i, j, hp, r);
-    const RayResult res = trace_ray<SPHERE, MODE>(T, r, n_lb, n_smp, tab);
+    const RayResult res = trace_ray<SPHERE, MODE, FLAGS == FWD_SAVE>(T, r, n_lb, n_smp, tab);
     out[lj * T.RW + li] = disc_fraction(res.alpha, T);
     if (FLAGS == FWD_SAVE) sample[lj * T.RW + li] = res.valid ? res.n : -1;
   }

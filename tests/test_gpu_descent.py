@@ -120,3 +120,24 @@ def test_scattered_missing_heights(ss, rows, width, share):
             grid = ss.shadow_cast(h, 20.0, math.radians(deg), az, RL, p)
             mixed = shuffled(ss, h, 20.0, math.radians(deg), az, p, 5)
             assert torch.equal(grid[~bad], mixed[~bad]), (deg, az, radius)
+
+
+@pytest.mark.parametrize("mode", ["DP", "UNIFORM", "EXACT", "POINT"])
+def test_recorded_sample_is_the_smallest(ss, mode):
+    """The deciding sample a forward records, with the early exits and without: the same on
+    every penumbra ray, and on a lit one the same or one before the exit over the tile's
+    top, never one that a run ended early would have hidden."""
+    h = torch.from_numpy(rough(257, 300, 1)).cuda()
+    for deg, az, radius in ((1.5, 0.7, MOON), (4.0, 3.9, math.inf), (12.0, 0.5 * math.pi, MOON)):
+        kw = dict(mode=getattr(ss, "SS_MODE_" + mode), radius_m=radius)
+        e = math.radians(deg)
+        s0, every = ss.shadow_cast_save(h, 20.0, e, az, RL, ss.Params(prune=0, **kw))
+        s1, quick = ss.shadow_cast_save(h, 20.0, e, az, RL, ss.Params(**kw))
+        assert torch.equal(s0, s1)
+        part = (s0 > 0) & (s0 < 1)
+        assert torch.equal(every[part], quick[part])
+        if mode != "EXACT":  # its walk passes over more on lit rays
+            lit = s0 >= 1
+            # a sample recorded with the exits lies before one found only without them
+            changed = lit & (every != quick)
+            assert bool((quick[changed] < every[changed]).all())
