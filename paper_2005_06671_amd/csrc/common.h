@@ -49,7 +49,7 @@ struct TileK {
   int prune;                 // 1: result-invariant early exits enabled
   int wg_group;              // per-tile kernels: workgroup ids are remapped within groups of
                              // this many (one device-full, a multiple of 8)
-  int ulev;                  // uniform stepping: mip level whose texels hold a chunk's path (chunk_level)
+  int ulev;                  // uniform stepping: chunk_level
   unsigned fit_err[SS_FITRUNS];  // run j: error bounds of the tip height's fits (fit_err_pack)
 };
 // The batched workspace holds one block per (tile, sun) pair, and how many
@@ -68,15 +68,15 @@ __device__ __forceinline__ unsigned finite_word(float top, unsigned key) {
   return __float_as_uint(top) ^ key;
 }
 
-// Uniform stepping looks at SS_CHUNK steps at a time, and at four such chunks.
+// Steps are taken SS_CHUNK at a time.
 #define SS_CHUNK 16
 
 // The finest mip level of whose texels two by two hold the taps of a chunk of
 // `step` texels per step: one texel there spans the chunk's travel (a tenth to
 // spare for tiles whose plane bends away) and the taps around its ends.
-inline int chunk_level(double step) {
+constexpr int chunk_level(double step) {
   int m = 0;
-  while (ldexp(1.0, m) < (SS_CHUNK - 1) * step * 1.1 + 2.0) ++m;
+  while ((double)(1LL << m) < (SS_CHUNK - 1) * step * 1.1 + 2.0) ++m;
   return m;
 }
 

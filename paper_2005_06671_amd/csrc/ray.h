@@ -1030,15 +1030,15 @@ __device__ __forceinline__ float step_t(const TileK& T, int k, float step) {
   return fmaf((float)k, step, T.half_delta);
 }
 
-// True when the n steps from step k (ray length t, texture parameter u) of every
+// True when the steps from ray length t (texture parameter u) to te of every
 // ray of the wavefront all clear `need` over the highest terrain their taps can
 // touch: the two by two texels of level m that hold the taps between the first
 // step's position and the last one's (the path is a line, so the rest lies
 // between).
 template <bool SPHERE>
 __device__ __forceinline__ bool steps_clear(const TileK& T, const Ray<SPHERE>& r, const Level& L,
-                                            int m, int k, int n, float t, float u, float need) {
-  const float ue = fminf(t_to_u(r, fminf(step_t(T, k + n - 1, T.ustep), T.ucap)), r.uexit);
+                                            int m, float t, float u, float te, float need) {
+  const float ue = fminf(t_to_u(r, fminf(te, T.ucap)), r.uexit);
   const float xa = floorf(fmaf(r.Kx, u, r.ox)), xb = floorf(fmaf(r.Kx, ue, r.ox));
   const float ya = floorf(fmaf(r.Ky, u, r.oy)), yb = floorf(fmaf(r.Ky, ue, r.oy));
   // taps i + floor and the next, clamped to the tile as the samples clamp theirs
@@ -1056,103 +1056,138 @@ __device__ __forceinline__ bool steps_clear(const TileK& T, const Ray<SPHERE>& r
   return lanes(!clear) == 0;
 }
 
-// Uniform stepping (Sec. 2, Fig. 1b): every step, smallest clearance, kept as
-// a tangent key; atan is taken once.  The first smallest step decides.
-//
-// The wavefront's steps run in chunks of SS_CHUNK.  With prune, steps that cannot
-// matter to any of its rays are passed over, four chunks at a time where that can
-// be shown and chunk by chunk otherwise; a chunk whose steps all count and whose
-// taps all lie inside the tile runs without clamps, two 8-byte gathers a step.
-// Bound by instruction issue (53 a step in such a chunk, 65 with the clamps and four
-// gathers): a 1024^2 tile at 1.5 deg, half-texel steps to 30 km, 764 us step by step,
-// 600 in chunks and 285 with the passing over, which looks at terrain maxima once
-// for 16 or 64 steps where most steps lie far above the terrain.
-//
-// KEEP: as in shadow_dp; every step before an exit is taken.
-template <bool SPHERE, bool KEEP>
-__device__ __forceinline__ RayResult shadow_uniform(const TileK& T, const Ray<SPHERE>& r, float top,
-                                                    unsigned& n_smp) {
-  RayResult res;
-  res.t = 0.0f;
-  res.u = 0.0f;
-  res.n = -1;
-  res.valid = 0;
-  float best = SS_INF;
-  auto take = [&](float t, float u, int k, float dh) {
-    n_smp++;
-    float num, den;
-    clearance_terms(r, t, dh, num, den);
-    const float key = tangent_key(num, den);
-    if (key < best) {
-      best = key;
-      res.t = t;
-      res.u = u;
-      res.n = k;
-      res.valid = 1;
-    }
-  };
-  const Level L0 = level_of(T, 0);
+// True when the taps of steps k .. k + n - 1 of every ray of the wavefront lie off the
+// tile's edges and all of those steps count.  u: the texture parameter of step k.
+template <bool SPHERE>
+__device__ __forceinline__ bool steps_whole(const TileK& T, const Ray<SPHERE>& r, float step, int k,
+                                            int n, float u) {
+  const float te = step_t(T, k + n - 1, step), ue = t_to_u(r, te);
+  const float xa = (float)r.i + fmaf(r.Kx, u, r.ox), xb = (float)r.i + fmaf(r.Kx, ue, r.ox);
+  const float ya = (float)r.j + fmaf(r.Ky, u, r.oy), yb = (float)r.j + fmaf(r.Ky, ue, r.oy);
+  const bool whole = te <= T.ucap && ue < r.uexit && fminf(xa, xb) >= 1.0f &&
+                     fminf(ya, yb) >= 1.0f && fmaxf(xa, xb) < (float)(T.W - 2) &&
+                     fmaxf(ya, yb) < (float)(T.H - 2);
+  return lanes(!whole) == 0;
+}
+
+// Keeps the smaller of `res` and the clearance of step k, whose tip lies dh above the
+// terrain; of equal ones the first.
+template <bool SPHERE>
+__device__ __forceinline__ void take_step(const Ray<SPHERE>& r, int k, float t, float u, float dh,
+                                          RayResult& res, unsigned& n_smp) {
+  n_smp++;
+  float num, den;
+  clearance_terms(r, t, dh, num, den);
+  const float key = tangent_key(num, den);
+  if (key < res.key) {
+    res.key = key;
+    res.t = t;
+    res.u = u;
+    res.n = k;
+    res.valid = 1;
+  }
+}
+
+// N steps from step k, for which steps_whole holds: as sample_at without the clamps,
+// two 8-byte gathers a step, four steps' gathers in flight.
+template <bool SPHERE, int N>
+__device__ __forceinline__ void steps_inside(const TileK& T, const Ray<SPHERE>& r, const Level& L0,
+                                             float step, int k, RayResult& res, unsigned& n_smp) {
   const int base = __mul24(r.j, L0.w) + r.i;
-  const int ma = min(T.ulev, T.L - 1), mb = min(T.ulev + 2, T.L - 1);
-  const bool skip = !KEEP && T.prune && heights_finite(T);
-  const bool wide = skip && T.lev[mb].w >= 2 && T.lev[mb].h >= 2;
-  const bool small = skip && T.lev[ma].w >= 2 && T.lev[ma].h >= 2;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    const float t = step_t(T, k + c, step);
+    const float u = t_to_u(r, t);
+    const float dx = fmaf(r.Kx, u, r.ox), dy = fmaf(r.Ky, u, r.oy);
+    const float flx = floorf(dx), fly = floorf(dy);
+    const float fx = dx - flx, fy = dy - fly;
+    const unsigned a = 4u * (unsigned)(__mul24((int)fly, L0.w) + ((int)flx + base));
+    const f32x2 lo = pair_at(L0, a), hi = pair_at(L0, a + 4u * (unsigned)L0.w);
+    const float h00 = lo.x - r.hp, h10 = lo.y - r.hp;
+    const float h01 = hi.x - r.hp, h11 = hi.y - r.hp;
+    const float hb = (1.0f - fy) * ((1.0f - fx) * h00 + fx * h10) +
+                     fy * ((1.0f - fx) * h01 + fx * h11);
+    take_step(r, k + c, t, u, tip_rise(r, T, t) - hb, res, n_smp);
+  }
+}
+
+// The smallest clearance over the steps k = 0, 1, ... of a ray up to the cap or the
+// tile edge, kept as a tangent key; the first smallest step decides.  res holds what is
+// known of the ray already.
+//
+// The wavefront's rays step together, in chunks of SS_CHUNK steps.  pass: steps that
+// cannot matter to any of the rays are passed over (steps_clear), four chunks where
+// that can be shown, else a chunk, else half of one.  lev: the mip level for a chunk.
+// Steps that all count and lie inside the tile run without clamps.
+//
+// Bound by instruction issue (53 a step inside, 65 with the clamps and four gathers;
+// 50 a look at the terrain's maxima) and by the gathers' latency, so half a chunk's
+// gathers are in flight at once.  A 1024^2 tile at 1.5 deg, one-texel steps to 30 km:
+// 764 us step by step, 600 without the clamps, 285 passing over 64 and 16 steps, 262
+// with the halves; eight gathers at a time 245.  A fourth size of 256 steps is worth
+// 2% or costs as much, and sizes that double and halve as they go cost 10% more.
+template <bool SPHERE>
+__device__ __forceinline__ void step_through(const TileK& T, const Ray<SPHERE>& r, float top,
+                                             float step, int lev, bool pass, RayResult& res,
+                                             unsigned& n_smp) {
+  constexpr int HALF = SS_CHUNK / 2, MID = 4 * SS_CHUNK;
+  const Level L0 = level_of(T, 0);
+  const int mh = min(max(lev - 1, 0), T.L - 1), ma = min(lev, T.L - 1);
+  const int mb = min(lev + 2, T.L - 1);
+  auto fits = [&](int m) { return pass && min(T.lev[m].w, T.lev[m].h) >= 2; };
+  const bool small = fits(ma), mid = fits(mb);
   bool done = false;
   for (int k = 0; k < (1 << 22) && !done; k += SS_CHUNK) {
-    const float t = step_t(T, k, T.ustep);
+    const float t = step_t(T, k, step);
     if (t > T.ucap) break;
     const float u = t_to_u(r, t);
     if (!(u < r.uexit)) break;
     if (T.prune) {
-      if (best <= -T.tan_rL) break;
-      const float need = need_tangent(T, best);
+      if (res.key <= -T.tan_rL) break;
+      const float need = need_tangent(T, res.key);
       if (clears(r, T, t, top, need)) break;
-      if (wide && (k & (4 * SS_CHUNK - 1)) == 0 &&
-          steps_clear(T, r, level_of(T, mb), mb, k, 4 * SS_CHUNK, t, u, need)) {
-        k += 3 * SS_CHUNK;
+      if (mid && (k & (MID - 1)) == 0 &&
+          steps_clear(T, r, level_of(T, mb), mb, t, u, step_t(T, k + MID - 1, step), need)) {
+        k += MID - SS_CHUNK;
         continue;
       }
-      if (small && steps_clear(T, r, level_of(T, ma), ma, k, SS_CHUNK, t, u, need)) continue;
+      if (small && steps_clear(T, r, level_of(T, ma), ma, t, u, step_t(T, k + SS_CHUNK - 1, step), need)) continue;
     }
-    // whole and inside for every ray: the last step counts, and both ends' taps
-    // lie off the edges
-    const float te = step_t(T, k + SS_CHUNK - 1, T.ustep), ue = t_to_u(r, te);
-    const float xa = (float)r.i + fmaf(r.Kx, u, r.ox), xb = (float)r.i + fmaf(r.Kx, ue, r.ox);
-    const float ya = (float)r.j + fmaf(r.Ky, u, r.oy), yb = (float)r.j + fmaf(r.Ky, ue, r.oy);
-    const bool whole = te <= T.ucap && ue < r.uexit && fminf(xa, xb) >= 1.0f &&
-                       fminf(ya, yb) >= 1.0f && fmaxf(xa, xb) < (float)(T.W - 2) &&
-                       fmaxf(ya, yb) < (float)(T.H - 2);
-    if (lanes(!whole) == 0) {
-#pragma unroll 4
-      for (int c = 0; c < SS_CHUNK; ++c) {
-        const float tc = step_t(T, k + c, T.ustep);
-        const float uc = t_to_u(r, tc);
-        // as sample_at, without the clamps
-        const float dx = fmaf(r.Kx, uc, r.ox), dy = fmaf(r.Ky, uc, r.oy);
-        const float flx = floorf(dx), fly = floorf(dy);
-        const float fx = dx - flx, fy = dy - fly;
-        const unsigned a = 4u * (unsigned)(__mul24((int)fly, L0.w) + ((int)flx + base));
-        const f32x2 lo = pair_at(L0, a), hi = pair_at(L0, a + 4u * (unsigned)L0.w);
-        const float h00 = lo.x - r.hp, h10 = lo.y - r.hp;
-        const float h01 = hi.x - r.hp, h11 = hi.y - r.hp;
-        const float hb = (1.0f - fy) * ((1.0f - fx) * h00 + fx * h10) +
-                         fy * ((1.0f - fx) * h01 + fx * h11);
-        take(tc, uc, k + c, tip_rise(r, T, tc) - hb);
+    if (steps_whole(T, r, step, k, SS_CHUNK, u)) {
+      for (int q = k; q < k + SS_CHUNK; q += HALF) {
+        const float tq = step_t(T, q, step);
+        if (small && steps_clear(T, r, level_of(T, mh), mh, tq, t_to_u(r, tq), step_t(T, q + HALF - 1, step),
+                                 need_tangent(T, res.key)))
+          continue;
+        steps_inside<SPHERE, HALF>(T, r, L0, step, q, res, n_smp);
       }
     } else {
       for (int c = 0; c < SS_CHUNK; ++c) {
-        const float tc = step_t(T, k + c, T.ustep);
+        const float tc = step_t(T, k + c, step);
         const float uc = t_to_u(r, tc);
         if (tc > T.ucap || !(uc < r.uexit)) {
           done = true;
           break;
         }
-        take(tc, uc, k + c, sample_at(r, T, tc, uc).dh);
+        take_step(r, k + c, tc, uc, sample_at(r, T, tc, uc).dh, res, n_smp);
       }
     }
   }
-  res.key = best;
-  res.alpha = angle_of(best);
+  res.alpha = angle_of(res.key);
+}
+
+// Uniform stepping (Sec. 2, Fig. 1b): every step.
+// KEEP: as in shadow_dp; every step before an exit is taken.
+template <bool SPHERE, bool KEEP>
+__device__ __forceinline__ RayResult shadow_uniform(const TileK& T, const Ray<SPHERE>& r, float top,
+                                                    unsigned& n_smp) {
+  RayResult res;
+  res.key = SS_INF;
+  res.t = 0.0f;
+  res.u = 0.0f;
+  res.n = -1;
+  res.valid = 0;
+  step_through(T, r, top, T.ustep, T.ulev, !KEEP && T.prune && heights_finite(T), res, n_smp);
   return res;
 }
 
@@ -1189,6 +1224,13 @@ __device__ __forceinline__ float bound_at(const TileK& T, const int* tab, int m,
 // bit-identical to uniform stepping at half a texel (prune = 0 evaluates
 // every sample).
 //
+// That walk is for tiles with missing or infinite heights, for prune = 0 and for the
+// forward that records the deciding sample (KEEP).  Otherwise the wavefront's rays step
+// through the grid together (step_through): 64 lanes at levels and samples of their own
+// run every branch of an iteration, so the walk took as long as its slowest ray at 130
+// instructions an iteration, mostly waiting for one gather.  Same results; 2048^2 tiles
+// at 1.5 deg, 0.2 deg: 912 to 1153 us and 2700 with the walk, 826 to 1022 and 1955 now.
+//
 // Branch and bound prunes best with a good incumbent: the descent (Sec. 3.2)
 // runs first and its deciding sample, a sample of the same grid computed by
 // the same arithmetic, seeds the minimum when it lies within the cap.  A ray
@@ -1212,6 +1254,11 @@ __device__ __forceinline__ RayResult shadow_exact(const TileK& T, const Ray<SPHE
       res = d;
       best = d.key;
     }
+  }
+  if (!KEEP && T.prune && heights_finite(T)) {
+    res.key = best;
+    step_through(T, r, top, T.half_delta, chunk_level(0.5), true, res, n_smp);
+    return res;
   }
   float need = need_tangent(T, best);
   const int mtop = T.L - 1;
