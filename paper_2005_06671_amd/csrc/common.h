@@ -65,7 +65,7 @@ __host__ __device__ inline unsigned finite_key(int W, int H) {
   return 0x5f3c9a17u ^ ((unsigned)W * 0x9e3779b1u) ^ ((unsigned)H * 0x85ebca6bu);
 }
 __device__ __forceinline__ unsigned finite_word(float top, unsigned key) {
-  return __float_as_uint(top) ^ key;
+  return __builtin_bit_cast(unsigned, top) ^ key;
 }
 
 // Steps are taken SS_CHUNK at a time.
