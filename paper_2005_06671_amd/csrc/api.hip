@@ -80,11 +80,12 @@ extern "C" int64_t ss_maxmip_floats(int32_t width, int32_t rows) {
   return ss_maxmip_level_offset(width, rows, levels_of(width, rows));
 }
 
+// from: levels up to this one are there already.
 static int32_t maxmip_build(const float* d_height, int32_t W, int32_t H, float* d_mm, int fuse,
-                            hipStream_t stream) {
+                            hipStream_t stream, int from = 0) {
   const int L = levels_of(W, H);
   if (fuse < 1 || fuse > 6) fuse = 6;
-  int src_m = 0;
+  int src_m = from;
   while (src_m < L - 1) {
     const int F = (L - 1 - src_m) < fuse ? (L - 1 - src_m) : fuse;
     int sw, sh;
@@ -141,8 +142,16 @@ extern "C" int32_t ss_bound_build(const float* d_height, int32_t width, int32_t 
   if (width == 0 || rows == 0) return (width >= 0 && rows >= 0) ? SS_OK : SS_ERR_INVALID_ARG;
   if (!size_ok(width, rows) || !d_height || !d_bound) return SS_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
-  SS_HIP(launch_block3_max(d_height, width, rows, d_bound, s));
-  return maxmip_build(d_bound, width, rows, d_bound + bound_base(width, rows), 6, s);
+  float* mm = d_bound + bound_base(width, rows);
+  const int L = levels_of(width, rows);
+  const int F = L - 1 < 6 ? L - 1 : 6;
+  int off[6], w[6], h[6];
+  for (int k = 0; k < F; ++k) {
+    off[k] = (int)ss_maxmip_level_offset(width, rows, 1 + k);
+    dims_of(width, rows, 1 + k, &w[k], &h[k]);
+  }
+  SS_HIP(launch_bound(d_height, width, rows, d_bound, mm, off, w, h, F, s));
+  return maxmip_build(d_bound, width, rows, mm, 6, s, F);
 }
 
 // ------------------------------------------------------------------------

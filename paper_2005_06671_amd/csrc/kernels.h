@@ -16,8 +16,11 @@ hipError_t launch_maxmip(const float* src, int sw, int sh, float* dst_base, cons
                          const int* dst_w, const int* dst_h, int F, const float* below, int bw,
                          int bh, int last, unsigned key, hipStream_t stream);
 
-// Tap-bound pyramid level 0: maximum over each texel's 3 x 3 block (clipped).
-hipError_t launch_block3_max(const float* src, int W, int H, float* dst, hipStream_t stream);
+// Tap-bound pyramid: level 0 (maximum over each texel's 3 x 3 block, clipped) and the
+// first F levels (F <= 6) of its maximum mipmap.
+hipError_t launch_bound(const float* src, int W, int H, float* level0, float* dst_base,
+                        const int* dst_off, const int* dst_w, const int* dst_h, int F,
+                        hipStream_t stream);
 
 void grid_for(const TileK& T, int ray_tile, int* nbx, int* nblocks);
 

@@ -17,6 +17,7 @@
 // and a barrier where fewer than five levels are written (a 4096^2 tile's first launch
 // 16.5 us before and 17.2 with it; both launches of a 256^2 tile 5.8 and 6.4).
 #include "kernels.h"
+#include "ray.h"
 
 namespace ss {
 
@@ -31,6 +32,125 @@ struct MipDst {
 };
 
 __device__ __forceinline__ float canon(float v) { return v + 0.0f; }  // -0 -> +0
+
+// The value a lane of the same 16 holds (DPP control CTRL); 0 where there is none.
+template <int CTRL>
+__device__ __forceinline__ float from_lane(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+// Writes F levels of one 64 x 64 block from its texels v (a 4 x 4 patch a thread,
+// -inf where there is none).  CHECK: with the answer on finite heights; mine: this
+// thread has seen another.
+template <bool CHECK>
+__device__ __forceinline__ void block_levels(int F, const float (&v)[4][4], bool mine, float* dst,
+                                             const MipDst& d, int bx, int by, float (&lds)[4][4],
+                                             int (&lds_bad)[4]) {
+  const int t = threadIdx.x;
+  const int c4 = t & 15, rg = t >> 4;
+  if (CHECK) {
+    const bool wave_bad = __any(mine);
+    if ((t & 63) == 0) lds_bad[t >> 6] = wave_bad;
+  }
+  // for the last level written, after a barrier: NaN hands the answer on, and the
+  // thread that writes the top's texel leaves it beside it
+  float mark = 0.0f;
+  bool bad = false;
+  auto gather = [&] {
+    __syncthreads();
+    if (!CHECK) return;
+    bad = (lds_bad[0] | lds_bad[1] | lds_bad[2] | lds_bad[3]) != 0;
+    mark = bad && !d.last ? __builtin_nanf("") : 0.0f;
+  };
+  auto verdict = [&](float top) {
+    if (CHECK && d.last)
+      reinterpret_cast<unsigned*>(dst)[d.off[F - 1] + 1] = bad ? ~finite_word(top, d.key)
+                                                               : finite_word(top, d.key);
+  };
+  if (CHECK && F < 5) gather();
+  // level +1: 2 x 2 per thread
+  float a[2][2];
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      a[r][c] = fmaxf(fmaxf(v[2 * r][2 * c], v[2 * r][2 * c + 1]),
+                      fmaxf(v[2 * r + 1][2 * c], v[2 * r + 1][2 * c + 1])) +
+                (CHECK && F == 1 ? mark : 0.0f);
+  {
+    const int w1 = d.w[0], h1 = d.h[0];
+    float* L1 = dst + d.off[0];
+    const int cc = bx * 32 + c4 * 2;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int rr = by * 32 + rg * 2 + r;
+      if (rr < h1) {
+        if ((w1 & 1) == 0 && cc + 1 < w1) {
+          *reinterpret_cast<float2*>(L1 + (size_t)rr * w1 + cc) = make_float2(a[r][0], a[r][1]);
+        } else {
+          if (cc < w1) L1[(size_t)rr * w1 + cc] = a[r][0];
+          if (cc + 1 < w1) L1[(size_t)rr * w1 + cc + 1] = a[r][1];
+        }
+      }
+    }
+  }
+  if (F == 1) {
+    if (t == 0) verdict(a[0][0]);
+    return;
+  }
+  // level +2: one value per thread
+  float b2 = fmaxf(fmaxf(a[0][0], a[0][1]), fmaxf(a[1][0], a[1][1]));
+  {
+    const int rr = by * 16 + rg, cc = bx * 16 + c4;
+    if (rr < d.h[1] && cc < d.w[1]) dst[d.off[1] + (size_t)rr * d.w[1] + cc] = b2 + (CHECK && F == 2 ? mark : 0.0f);
+  }
+  if (F == 2) {
+    if (t == 0) verdict(b2);
+    return;
+  }
+  // level +3: lanes (c4, c4^1) x (rg, rg^1) of the same wavefront
+  float b3 = fmaxf(b2, __shfl_xor(b2, 1, 64));
+  b3 = fmaxf(b3, __shfl_xor(b3, 16, 64));
+  if (((c4 | rg) & 1) == 0) {
+    const int rr = by * 8 + (rg >> 1), cc = bx * 8 + (c4 >> 1);
+    if (rr < d.h[2] && cc < d.w[2]) dst[d.off[2] + (size_t)rr * d.w[2] + cc] = b3 + (CHECK && F == 3 ? mark : 0.0f);
+  }
+  if (F == 3) {
+    if (t == 0) verdict(b3);
+    return;
+  }
+  // level +4: lanes (c4, c4^2) x (rg, rg^2)
+  float b4 = fmaxf(b3, __shfl_xor(b3, 2, 64));
+  b4 = fmaxf(b4, __shfl_xor(b4, 32, 64));
+  if (((c4 | rg) & 3) == 0) {
+    const int rr = by * 4 + (rg >> 2), cc = bx * 4 + (c4 >> 2);
+    if (rr < d.h[3] && cc < d.w[3]) dst[d.off[3] + (size_t)rr * d.w[3] + cc] = b4 + (CHECK && F == 4 ? mark : 0.0f);
+    lds[rg >> 2][c4 >> 2] = b4;
+  }
+  if (F == 4) {
+    if (t == 0) verdict(b4);
+    return;
+  }
+  gather();
+  if (t < 4) {
+    const int r5 = t >> 1, c5 = t & 1;
+    const float m5 = fmaxf(fmaxf(lds[2 * r5][2 * c5], lds[2 * r5][2 * c5 + 1]),
+                           fmaxf(lds[2 * r5 + 1][2 * c5], lds[2 * r5 + 1][2 * c5 + 1]));
+    const int rr = by * 2 + r5, cc = bx * 2 + c5;
+    if (rr < d.h[4] && cc < d.w[4]) dst[d.off[4] + (size_t)rr * d.w[4] + cc] = m5 + (CHECK && F == 5 ? mark : 0.0f);
+    if (F == 5 && t == 0) verdict(m5);
+  }
+  if (F == 5) return;
+  if (t == 0) {
+    float m6 = lds[0][0];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) m6 = fmaxf(m6, lds[r][c]);
+    if (by < d.h[5] && bx < d.w[5]) dst[d.off[5] + (size_t)by * d.w[5] + bx] = m6 + (CHECK ? mark : 0.0f);
+    verdict(m6);
+  }
+}
 
 template <int F>
 __global__ __launch_bounds__(256) void maxmip_kernel(const float* src, int sw, int sh, float* dst,
@@ -82,137 +202,114 @@ __global__ __launch_bounds__(256) void maxmip_kernel(const float* src, int sw, i
       }
     }
   }
-  const bool wave_bad = __any(mine);
-  if ((t & 63) == 0) lds_bad[t >> 6] = wave_bad;
-  // for the last level written, after a barrier: NaN hands the answer on, and the
-  // thread that writes the top's texel leaves it beside it
-  float mark = 0.0f;
-  bool bad = false;
-  auto gather = [&] {
-    __syncthreads();
-    bad = (lds_bad[0] | lds_bad[1] | lds_bad[2] | lds_bad[3]) != 0;
-    mark = bad && !d.last ? __builtin_nanf("") : 0.0f;
-  };
-  auto verdict = [&](float top) {
-    if (d.last)
-      reinterpret_cast<unsigned*>(dst)[d.off[F - 1] + 1] = bad ? ~finite_word(top, d.key)
-                                                               : finite_word(top, d.key);
-  };
-  if (F < 5) gather();
-  // level +1: 2 x 2 per thread
-  float a[2][2];
+  block_levels<true>(F, v, mine, dst, d, bx, by, lds, lds_bad);
+}
+
+// Tap-bound level 0: the maximum over the 3 x 3 block around each texel, clipped to
+// the tile (repeating the edge row or column gives the same maximum), -0 stored as +0;
+// and the first F levels of its maximum mipmap in the same pass.
+//
+// Bound by memory: the heights are read once and every level is written once, where a
+// launch for level 0 and one for the mipmap read level 0 again (a 4096^2 tile: 24.8 and
+// 16.4 us; 26.4 now, 38.6 with the patch read float by float).  Each thread takes the
+// columns' maxima over three rows of its 4 x 4 patch and the columns beside the patch
+// from the lanes next to it (DPP, 16 lanes to a row); the block's outer columns are
+// loaded, from the L2 that neighbouring blocks share (xcd_remap: 1.5 us of it).
+// VEC: 16-byte rows; a template and not a branch, as a branch's loads were merged into
+// single floats.
+template <bool VEC>
+__global__ __launch_bounds__(256) void bound_kernel(const float* __restrict__ src, int W, int H,
+                                                    float* __restrict__ level0, float* dst, MipDst d,
+                                                    int F, int nbx) {
+  __shared__ float lds[4][4];
+  __shared__ int unused[4];
+  const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);  // neighbours in one L2
+  const int bx = b % nbx, by = b / nbx;
+  const int t = threadIdx.x;
+  const int c4 = t & 15, rg = t >> 4;
+  const int col0 = bx * 64 + c4 * 4, row0 = by * 64 + rg * 4;
+  const float NEG = -__builtin_inff();
+  // the block's outer column of this lane, where it has one
+  const int side = c4 == 0 ? max(col0 - 1, 0) : min(col0 + 4, W - 1);
+  const bool outer = c4 == 0 || c4 == 15;
+  // six rows: the patch's and one on either side, repeated at the tile's edge
+  float q[6][4], o[6];
+  auto row_at = [&](int r) { return src + (size_t)min(max(row0 + r - 1, 0), H - 1) * W; };
+  if (VEC) {
+    // W is a multiple of 4: a patch lies inside or beyond the edge as a whole, and
+    // one beyond it repeats the last column for the lane before it
+    float4 x[6];
 #pragma unroll
-  for (int r = 0; r < 2; ++r)
+    for (int r = 0; r < 6; ++r)
+      x[r] = *reinterpret_cast<const float4*>(row_at(r) + min(col0, W - 4));
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-      a[r][c] = fmaxf(fmaxf(v[2 * r][2 * c], v[2 * r][2 * c + 1]),
-                      fmaxf(v[2 * r + 1][2 * c], v[2 * r + 1][2 * c + 1])) +
-                (F == 1 ? mark : 0.0f);
-  {
-    const int w1 = d.w[0], h1 = d.h[0];
-    float* L1 = dst + d.off[0];
-    const int cc = bx * 32 + c4 * 2;
+    for (int r = 0; r < 6; ++r) {
+      q[r][0] = col0 < W ? x[r].x : x[r].w;
+      q[r][1] = x[r].y;
+      q[r][2] = x[r].z;
+      q[r][3] = x[r].w;
+    }
+  } else {
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int rr = by * 32 + rg * 2 + r;
-      if (rr < h1) {
-        if ((w1 & 1) == 0 && cc + 1 < w1) {
-          *reinterpret_cast<float2*>(L1 + (size_t)rr * w1 + cc) = make_float2(a[r][0], a[r][1]);
-        } else {
-          if (cc < w1) L1[(size_t)rr * w1 + cc] = a[r][0];
-          if (cc + 1 < w1) L1[(size_t)rr * w1 + cc + 1] = a[r][1];
-        }
+    for (int r = 0; r < 6; ++r)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) q[r][c] = row_at(r)[min(col0 + c, W - 1)];
+  }
+#pragma unroll
+  for (int r = 0; r < 6; ++r) o[r] = outer ? row_at(r)[side] : NEG;
+  float v[4][4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float m[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) m[c] = fmaxf(fmaxf(q[r][c], q[r + 1][c]), q[r + 2][c]);
+    const float mo = fmaxf(fmaxf(o[r], o[r + 1]), o[r + 2]);
+    float left = from_lane<0x111>(m[3]), right = from_lane<0x101>(m[0]);  // row_shr:1, row_shl:1
+    if (c4 == 0) left = mo;
+    if (c4 == 15) right = mo;
+    v[r][0] = canon(fmaxf(fmaxf(left, m[0]), m[1]));
+    v[r][1] = canon(fmaxf(fmaxf(m[0], m[1]), m[2]));
+    v[r][2] = canon(fmaxf(fmaxf(m[1], m[2]), m[3]));
+    v[r][3] = canon(fmaxf(fmaxf(m[2], m[3]), right));
+    const int row = row0 + r;
+    if (VEC) {
+      const bool in = row < H && col0 < W;
+      if (in)
+        *reinterpret_cast<float4*>(level0 + (size_t)row * W + col0) =
+            make_float4(v[r][0], v[r][1], v[r][2], v[r][3]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[r][c] = in ? v[r][c] : NEG;
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (row < H && col0 + c < W)
+          level0[(size_t)row * W + col0 + c] = v[r][c];
+        else
+          v[r][c] = NEG;
       }
     }
   }
-  if (F == 1) {
-    if (t == 0) verdict(a[0][0]);
-    return;
-  }
-  // level +2: one value per thread
-  float b2 = fmaxf(fmaxf(a[0][0], a[0][1]), fmaxf(a[1][0], a[1][1]));
-  {
-    const int rr = by * 16 + rg, cc = bx * 16 + c4;
-    if (rr < d.h[1] && cc < d.w[1]) dst[d.off[1] + (size_t)rr * d.w[1] + cc] = b2 + (F == 2 ? mark : 0.0f);
-  }
-  if (F == 2) {
-    if (t == 0) verdict(b2);
-    return;
-  }
-  // level +3: lanes (c4, c4^1) x (rg, rg^1) of the same wavefront
-  float b3 = fmaxf(b2, __shfl_xor(b2, 1, 64));
-  b3 = fmaxf(b3, __shfl_xor(b3, 16, 64));
-  if (((c4 | rg) & 1) == 0) {
-    const int rr = by * 8 + (rg >> 1), cc = bx * 8 + (c4 >> 1);
-    if (rr < d.h[2] && cc < d.w[2]) dst[d.off[2] + (size_t)rr * d.w[2] + cc] = b3 + (F == 3 ? mark : 0.0f);
-  }
-  if (F == 3) {
-    if (t == 0) verdict(b3);
-    return;
-  }
-  // level +4: lanes (c4, c4^2) x (rg, rg^2)
-  float b4 = fmaxf(b3, __shfl_xor(b3, 2, 64));
-  b4 = fmaxf(b4, __shfl_xor(b4, 32, 64));
-  if (((c4 | rg) & 3) == 0) {
-    const int rr = by * 4 + (rg >> 2), cc = bx * 4 + (c4 >> 2);
-    if (rr < d.h[3] && cc < d.w[3]) dst[d.off[3] + (size_t)rr * d.w[3] + cc] = b4 + (F == 4 ? mark : 0.0f);
-    lds[rg >> 2][c4 >> 2] = b4;
-  }
-  if (F == 4) {
-    if (t == 0) verdict(b4);
-    return;
-  }
-  gather();
-  if (t < 4) {
-    const int r5 = t >> 1, c5 = t & 1;
-    const float m5 = fmaxf(fmaxf(lds[2 * r5][2 * c5], lds[2 * r5][2 * c5 + 1]),
-                           fmaxf(lds[2 * r5 + 1][2 * c5], lds[2 * r5 + 1][2 * c5 + 1]));
-    const int rr = by * 2 + r5, cc = bx * 2 + c5;
-    if (rr < d.h[4] && cc < d.w[4]) dst[d.off[4] + (size_t)rr * d.w[4] + cc] = m5 + (F == 5 ? mark : 0.0f);
-    if (F == 5 && t == 0) verdict(m5);
-  }
-  if (F == 5) return;
-  if (t == 0) {
-    float m6 = lds[0][0];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) m6 = fmaxf(m6, lds[r][c]);
-    if (by < d.h[5] && bx < d.w[5]) dst[d.off[5] + (size_t)by * d.w[5] + bx] = m6 + mark;
-    verdict(m6);
-  }
+  if (F > 0) block_levels<false>(F, v, false, dst, d, bx, by, lds, unused);
 }
 
-// Tap-bound level 0: the maximum over the 3 x 3 block around each texel,
-// clipped to the tile (repeating the edge row or column gives the same
-// maximum), -0 stored as +0.  One thread per column strip of 8 rows: each row's
-// 3-wide maximum is loaded once and the 3-row window slides down in registers.
-__global__ __launch_bounds__(256) void block3_max_kernel(const float* __restrict__ src, int W, int H,
-                                                         float* __restrict__ dst) {
-  const int x = blockIdx.x * 256 + threadIdx.x;
-  const int y0 = blockIdx.y * 8;
-  if (x >= W) return;
-  const int xl = max(x - 1, 0), xr = min(x + 1, W - 1);
-  auto row_max = [&](int y) {
-    const float* p = src + (size_t)y * W;
-    return fmaxf(fmaxf(p[xl], p[x]), p[xr]);
-  };
-  float a = row_max(max(y0 - 1, 0));
-  float b = row_max(y0);
-  for (int k = 0; k < 8; ++k) {
-    const int y = y0 + k;
-    if (y >= H) break;
-    const float c = row_max(min(y + 1, H - 1));
-    dst[(size_t)y * W + x] = canon(fmaxf(fmaxf(a, b), c));
-    a = b;
-    b = c;
+hipError_t launch_bound(const float* src, int W, int H, float* level0, float* dst_base,
+                        const int* dst_off, const int* dst_w, const int* dst_h, int F,
+                        hipStream_t stream) {
+  MipDst d{};
+  for (int k = 0; k < F; ++k) {
+    d.off[k] = dst_off[k];
+    d.w[k] = dst_w[k];
+    d.h[k] = dst_h[k];
   }
-}
-
-hipError_t launch_block3_max(const float* src, int W, int H, float* dst, hipStream_t stream) {
-  if (W <= 0 || H <= 0) return hipSuccess;
-  dim3 grid((W + 255) / 256, (H + 7) / 8), block(256);
-  hipLaunchKernelGGL(block3_max_kernel, grid, block, 0, stream, src, W, H, dst);
+  const int nbx = (W + 63) / 64, nby = (H + 63) / 64;
+  const int vec_ok = W % 4 == 0 && ((reinterpret_cast<uintptr_t>(src) |
+                                     reinterpret_cast<uintptr_t>(level0)) & 15) == 0;
+  if (vec_ok)
+    hipLaunchKernelGGL(bound_kernel<true>, dim3(nbx * nby), dim3(256), 0, stream, src, W, H, level0,
+                       dst_base, d, F, nbx);
+  else
+    hipLaunchKernelGGL(bound_kernel<false>, dim3(nbx * nby), dim3(256), 0, stream, src, W, H, level0,
+                       dst_base, d, F, nbx);
   return hipGetLastError();
 }
 
