@@ -76,7 +76,7 @@ __device__ __forceinline__ unsigned finite_word(float top, unsigned key) {
 // spare for tiles whose plane bends away) and the taps around its ends.
 constexpr int chunk_level(double step) {
   int m = 0;
-  while ((double)(1LL << m) < (SS_CHUNK - 1) * step * 1.1 + 2.0) ++m;
+  while (m < SS_MAXLEV && (double)(1LL << m) < (SS_CHUNK - 1) * step * 1.1 + 2.0) ++m;
   return m;
 }
 

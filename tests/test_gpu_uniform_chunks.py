@@ -120,3 +120,14 @@ def test_word_on_finite_heights(ss, rows, width, fuse):
             want = torch.fmax(torch.fmax(want[::2, ::2], want[1::2, ::2]),
                               torch.fmax(want[::2, 1::2], want[1::2, 1::2]))
             assert torch.equal(torch.nan_to_num(got.cpu(), nan=1e30), torch.nan_to_num(want, nan=1e30)), (y, x)
+
+
+@pytest.mark.parametrize("step", [1e4, 1e9, 1e30, 1e300])
+def test_steps_longer_than_any_tile(ss, step):
+    """A step of any finite length is accepted: one sample, or none once it overflows."""
+    h = rough(65, 130, 9).cuda()
+    print("step", step, flush=True)
+    kw = dict(mode=ss.SS_MODE_UNIFORM, uniform_step=step, radius_m=MOON)
+    quick = ss.shadow_cast(h, 20.0, math.radians(1.5), 0.7, RL, ss.Params(**kw))
+    every = ss.shadow_cast(h, 20.0, math.radians(1.5), 0.7, RL, ss.Params(prune=0, **kw))
+    assert torch.equal(quick, every)
