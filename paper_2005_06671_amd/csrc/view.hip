@@ -206,6 +206,17 @@ __device__ __forceinline__ float vreach_near(float g, float n, float m, float d,
   return den * (float)sg > 0.0f ? fmaf(g, n, m) * vrcp(den) : INFINITY;
 }
 
+// The same with rounded divisions, on axis 0 (x) or 1.
+template <bool SPHERE>
+__device__ __forceinline__ float vreach(const ViewK& K, const VRay<SPHERE>& r, int axis, float g,
+                                        int sg) {
+  const float G = (g - (axis == 0 ? K.cx0 : K.cy0)) * K.texel;
+  const float e = axis == 0 ? r.ex : r.ey, v = axis == 0 ? r.vx : r.vy;
+  const float den = SPHERE ? fmaf(-G * K.invR, r.vz, v) : v;
+  if (sg == 0 || !(den * (float)sg > 0.0f)) return INFINITY;
+  return SPHERE ? fmaf(G, r.ez * K.invR, G - e) / den : (G - e) / den;
+}
+
 // Motion sign of q along an axis; below the threshold the ray's whole path
 // moves less than a small fraction of a texel and counts as still.
 template <bool SPHERE>
@@ -274,12 +285,22 @@ __device__ VHit view_dense(const ViewK& K, const VRay<SPHERE>& r, float t0, floa
   return h;
 }
 
-// Hierarchical mode: front-to-back walk over the tap-bound pyramid.
-template <bool SPHERE>
+// Hierarchical mode: front-to-back walk over the tap-bound pyramid.  COUNT: the
+// caller asks for the samples and cells the walk visits; they are counted with the
+// rounded forms throughout, as a cell or two in a thousand rays depends on a last bit
+// (hits do not).
+template <bool SPHERE, bool COUNT>
 __device__ VHit view_hier(const ViewK& K, const VTab& lt, const VRay<SPHERE>& r, float t0,
                           float t1, float eyen, float hs) {
   VHit h{-1, 0, 0, 0.0f};
   const VNear<SPHERE> v = vnear_of<SPHERE>(K, r, hs);
+  auto position = [&](float at, float& qx, float& qy) {
+    if (COUNT)
+      vq<SPHERE>(K, r, at, qx, qy);
+    else
+      vq_near<SPHERE>(K, r, at, qx, qy);
+  };
+  auto height = [&](float at) { return COUNT ? vH<SPHERE>(K, r, at) : vH_near<SPHERE>(K, r, v, at); };
   float t = t0;
   // start three levels below the top (cells of 1/8 of the tile): every ray
   // below the shell would descend through the top levels anyway, and after a
@@ -287,7 +308,7 @@ __device__ VHit view_hier(const ViewK& K, const VTab& lt, const VRay<SPHERE>& r,
   int m = max(K.L - 4, 0), cx = 0, cy = 0;
   if (m < K.L - 1) {
     float qx, qy;
-    vq_near<SPHERE>(K, r, t, qx, qy);
+    position(t, qx, qy);
     cx = min(max((int)floorf(qx * lt.ip[m]), 0), lt.lw[m] - 1);
     cy = min(max((int)floorf(qy * lt.ip[m]), 0), lt.lh[m] - 1);
   }
@@ -296,12 +317,14 @@ __device__ VHit view_hier(const ViewK& K, const VTab& lt, const VRay<SPHERE>& r,
     // exit of the current cell through its far lines in the motion direction
     const float gx = (float)((r.sgx > 0 ? cx + 1 : cx) << m);
     const float gy = (float)((r.sgy > 0 ? cy + 1 : cy) << m);
-    const float tx = vreach_near(gx, v.n, v.mx, v.d, v.dx, r.sgx);
-    const float ty = vreach_near(gy, v.n, v.my, v.d, v.dy, r.sgy);
+    const float tx = COUNT ? vreach<SPHERE>(K, r, 0, gx, r.sgx)
+                           : vreach_near(gx, v.n, v.mx, v.d, v.dx, r.sgx);
+    const float ty = COUNT ? vreach<SPHERE>(K, r, 1, gy, r.sgy)
+                           : vreach_near(gy, v.n, v.my, v.d, v.dy, r.sgy);
     const float te = fmaxf(fminf(tx, ty), t);
     const float tb = fminf(te, t1);
     const float tm = fminf(fmaxf(r.t_hmin, t), tb);
-    const float Hmin = vH_near<SPHERE>(K, r, v, tm);
+    const float Hmin = height(tm);
     const float margin = fmaf(K.m_rel, eyen + tb, K.m_abs);
     const float Bm = vbound(K, lt, m, cx, cy) + margin;
     bool pass = Hmin > Bm;
@@ -310,15 +333,21 @@ __device__ VHit view_hier(const ViewK& K, const VTab& lt, const VRay<SPHERE>& r,
       // until the tangent comes down to Bm the ray passes above every tap of
       // the cell, and those samples are skipped (the slope, (b + t) / |P| on
       // the sphere, carries an allowance for its FP32 error of ~2e-7)
-      const float Ht = vH_near<SPHERE>(K, r, v, t);
-      const float slope = SPHERE ? (r.b + t) * vrcp(K.R + Ht) : r.vz;
-      const float rate = 4e-7f - slope;
-      if (Ht > Bm && rate > 0.0f) t = fminf(fmaf(Ht - Bm, vrcp(rate), t), tb);
+      const float Ht = height(t);
+      if (COUNT) {
+        const float slope = SPHERE ? (r.b + t) / (K.R + Ht) : r.vz;
+        const float rate = 2e-7f - slope;
+        if (Ht > Bm && rate > 0.0f) t = fminf(t + (Ht - Bm) / rate, tb);
+      } else {
+        const float slope = SPHERE ? (r.b + t) * vrcp(K.R + Ht) : r.vz;
+        const float rate = 4e-7f - slope;
+        if (Ht > Bm && rate > 0.0f) t = fminf(fmaf(Ht - Bm, vrcp(rate), t), tb);
+      }
     }
     if (!pass && m > 0) {
       // descend into the child that holds q(t) (clamped to this cell)
       float qx, qy;
-      vq_near<SPHERE>(K, r, t, qx, qy);
+      position(t, qx, qy);
       --m;
       const int kx = (int)floorf(qx * lt.ip[m]), ky = (int)floorf(qy * lt.ip[m]);
       cx = min(max(kx, 2 * cx), min(2 * cx + 1, lt.lw[m] - 1));
@@ -356,7 +385,7 @@ __device__ VHit view_hier(const ViewK& K, const VTab& lt, const VRay<SPHERE>& r,
   return h;
 }
 
-template <bool SPHERE, int MODE>
+template <bool SPHERE, int MODE, bool COUNT>
 __global__ __launch_bounds__(256) void view_kernel(ViewK K, float* __restrict__ out_t,
                                                    float2* __restrict__ out_xy,
                                                    int2* __restrict__ out_steps) {
@@ -444,7 +473,7 @@ __global__ __launch_bounds__(256) void view_kernel(ViewK K, float* __restrict__ 
     if (t_lo < t_hi) {
       const float eyen = sqrtf(fmaf(r.ex, r.ex, fmaf(r.ey, r.ey, r.ez * r.ez)));
       h = MODE == SS_VIEW_DENSE ? view_dense<SPHERE>(K, r, t_lo, t_hi)
-                                : view_hier<SPHERE>(K, lt, r, t_lo, t_hi, eyen, hs);
+                                : view_hier<SPHERE, COUNT>(K, lt, r, t_lo, t_hi, eyen, hs);
     }
   }
   const unsigned k = __umul24((unsigned)py, (unsigned)K.img_w) + (unsigned)px;
@@ -473,9 +502,11 @@ void view_launch(const ViewK& K, int mode, float* t, float* xy, int* steps, hipS
   float2* q = reinterpret_cast<float2*>(xy);
   int2* st = reinterpret_cast<int2*>(steps);
   if (mode == SS_VIEW_DENSE)
-    hipLaunchKernelGGL((view_kernel<SPHERE, SS_VIEW_DENSE>), grid, block, 0, s, K, t, q, st);
+    hipLaunchKernelGGL((view_kernel<SPHERE, SS_VIEW_DENSE, false>), grid, block, 0, s, K, t, q, st);
+  else if (steps)
+    hipLaunchKernelGGL((view_kernel<SPHERE, SS_VIEW_HIER, true>), grid, block, 0, s, K, t, q, st);
   else
-    hipLaunchKernelGGL((view_kernel<SPHERE, SS_VIEW_HIER>), grid, block, 0, s, K, t, q, st);
+    hipLaunchKernelGGL((view_kernel<SPHERE, SS_VIEW_HIER, false>), grid, block, 0, s, K, t, q, st);
 }
 
 }  // namespace

@@ -36,3 +36,19 @@ def test_walk_equals_dense(ss, kind, radius):
         td, xyd = ss.view_cast(h, texel, ss.Camera(mode=ss.SS_VIEW_DENSE, **c), radius, bound)
         assert torch.equal(t, td)
         assert torch.equal(xy.nan_to_num(-9.0), xyd.nan_to_num(-9.0))
+
+
+@pytest.mark.parametrize("radius", [1737400.0, 6.0e4, math.inf])
+def test_counting_walk_hits_the_same(ss, radius):
+    """The walk that counts its samples and cells keeps rounded cell geometry: same hits."""
+    rng = np.random.default_rng(4)
+    h = torch.from_numpy(rng.normal(0, 30, (256, 200)).astype(np.float32)).cuda()
+    bound = ss.bound_build(h)
+    for kind in ("oblique", "grazing", "flyover"):
+        print("counting", kind, radius, flush=True)
+        cam = ss.Camera(**view_scene(kind, 150, 101, 200, 256, 10.0, None))
+        t, xy = ss.view_cast(h, 10.0, cam, radius, bound)
+        tc, xyc, steps = ss.view_cast(h, 10.0, cam, radius, bound, steps=True)
+        assert torch.equal(t, tc)
+        assert torch.equal(xy.nan_to_num(-9.0), xyc.nan_to_num(-9.0))
+        assert bool((steps >= 0).all()) and bool((steps[torch.isfinite(t)][:, 0] > 0).all())
