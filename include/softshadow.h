@@ -88,8 +88,9 @@ typedef struct {
 /* One heightfield tile.  `maxmip` holds levels >= 1 of its maximum mipmap in
  * the packed layout below (built by ss_maxmip_build); `bound` holds its
  * tap-bound pyramid (built by ss_bound_build), read by SS_MODE_EXACT only and
- * may be NULL otherwise.  The per-tile calls only read both; the batched call
- * and a plan's graph (re)build them from `height`, so they are not const.
+ * may be NULL otherwise.  The per-tile calls only read both (but for the record
+ * after the mipmap's top, see ss_maxmip_build); the batched call and a plan's
+ * graph (re)build them from `height`, so they are not const.
  *
  * Ray window: rays start only at texels (i, j) with ray_x0 <= i < ray_x0 +
  * ray_w and ray_y0 <= j < ray_y0 + ray_h, while they see the whole tile.  A
@@ -126,6 +127,9 @@ int64_t ss_maxmip_floats(int32_t width, int32_t rows);
  * The float after the top texel (inside the total size) records whether every
  * height is finite: stepping passes over terrain only where that is known, so a
  * mipmap that was not built here is correct to use but slower to step through.
+ * Per-tile calls in SS_MODE_UNIFORM and SS_MODE_EXACT (prune = 1, nothing
+ * recorded) look at the heights again and take that record back if one has gone
+ * missing since the build; nothing else in a mipmap changes after it.
  * width or rows == 0 is an empty no-op. */
 int32_t ss_maxmip_build(const float* d_height, int32_t width, int32_t rows, float* d_maxmip,
                         int32_t fuse_depth, void* stream);

@@ -46,7 +46,8 @@ struct TileK {
   int nseg;                  // number of concatenated runs
   float tau[SS_MAXSEG + 1];  // ray length where run j starts (tau[nseg] = end)
   unsigned run[SS_MAXSEG];   // run j: grid index of its start, and its top mip level (run_pack)
-  int prune;                 // 1: result-invariant early exits enabled
+  int prune;                 // 1: result-invariant early exits enabled; 2: but stepping passes
+                             // over nothing (the heights may not all be finite)
   int wg_group;              // per-tile kernels: workgroup ids are remapped within groups of
                              // this many (one device-full, a multiple of 8)
   int ulev;                  // uniform stepping: chunk_level
@@ -59,8 +60,10 @@ static_assert(sizeof(TileK) == SS_TILEK_BYTES, "the parameter block's size is pa
 
 // The word after the mipmap's top texel: finite_word(top, key) when every height of
 // the tile is a finite number (any other value: not known to be).  The tile's size
-// and top are in it so that a word left by another tile in the same memory does not
-// pass for it.
+// and top are in it so that a word left by another tile in the same memory hardly
+// passes for it.  It says what a build saw, and heights may have gone missing since
+// (maxima do not show it), so a call that relies on it has the heights looked at first
+// (launch_finite_check).
 __host__ __device__ inline unsigned finite_key(int W, int H) {
   return 0x5f3c9a17u ^ ((unsigned)W * 0x9e3779b1u) ^ ((unsigned)H * 0x85ebca6bu);
 }

@@ -16,6 +16,10 @@ hipError_t launch_maxmip(const float* src, int sw, int sh, float* dst_base, cons
                          const int* dst_w, const int* dst_h, int F, const float* below, int bw,
                          int bh, int last, unsigned key, hipStream_t stream);
 
+// Takes back the word on finite heights beside the mipmap's top (finite_word) where the
+// tile holds a height that is missing or infinite by now.
+hipError_t launch_finite_check(const TileK& T, hipStream_t stream);
+
 // Tap-bound pyramid: level 0 (maximum over each texel's 3 x 3 block, clipped) and the
 // first F levels (F <= 6) of its maximum mipmap.
 hipError_t launch_bound(const float* src, int W, int H, float* level0, float* dst_base,

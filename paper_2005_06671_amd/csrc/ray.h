@@ -195,8 +195,9 @@ __device__ __forceinline__ float mip_at(const TileK& T, int m, int cx, int cy) {
 }
 
 // True when every height of the tile is known to be a finite number (the mipmap's
-// build says so).  A sample that touches a missing or infinite height can count as
-// in shadow whatever the maxima say, so only then may samples be passed over that
+// build says so, and the host has had the heights looked at again where a call
+// relies on it).  A sample that touches a missing or infinite height can count as in
+// shadow whatever the maxima say, so only then may samples be passed over that
 // stepping through the run would have reached.
 __device__ __forceinline__ bool heights_finite(const TileK& T) {
   if (T.L < 2) return false;
@@ -1187,7 +1188,7 @@ __device__ __forceinline__ RayResult shadow_uniform(const TileK& T, const Ray<SP
   res.u = 0.0f;
   res.n = -1;
   res.valid = 0;
-  step_through(T, r, top, T.ustep, T.ulev, !KEEP && T.prune && heights_finite(T), res, n_smp);
+  step_through(T, r, top, T.ustep, T.ulev, !KEEP && T.prune == 1 && heights_finite(T), res, n_smp);
   return res;
 }
 
@@ -1255,7 +1256,7 @@ __device__ __forceinline__ RayResult shadow_exact(const TileK& T, const Ray<SPHE
       best = d.key;
     }
   }
-  if (!KEEP && T.prune && heights_finite(T)) {
+  if (!KEEP && T.prune == 1 && heights_finite(T)) {
     res.key = best;
     step_through(T, r, top, T.half_delta, chunk_level(0.5), true, res, n_smp);
     return res;
