@@ -71,25 +71,21 @@ def maxmip_level_offset(width: int, rows: int, level: int) -> int:
 
 
 @lru_cache(maxsize=256)
-def _level_pieces(width: int, rows: int) -> tuple:
-    """Sizes that cut a packed mipmap into its levels and the padding after each, and the
-    levels' shapes: ([floats, padding, ...], [(rows_m, width_m), ...])."""
-    sizes, shapes = [], []
+def _level_spans(width: int, rows: int) -> list:
+    """(offset, floats, (rows_m, width_m)) of levels 1..L-1 in a packed mipmap."""
+    spans = []
     w, r = width, rows
     for m in range(1, maxmip_levels(width, rows)):
         w, r = (w + 1) // 2, (r + 1) // 2
-        here = maxmip_level_offset(width, rows, m)
-        sizes += [w * r, maxmip_level_offset(width, rows, m + 1) - here - w * r]
-        shapes.append((r, w))
-    return sizes, shapes
+        spans.append((maxmip_level_offset(width, rows, m), w * r, (r, w)))
+    return spans
 
 
-def _unpack(mm: torch.Tensor, width: int, rows: int) -> list:
-    sizes, shapes = _level_pieces(width, rows)
-    if not shapes:
-        return []
-    pieces = mm[:maxmip_floats(width, rows)].split(sizes)
-    return [p.view(s) for p, s in zip(pieces[::2], shapes)]
+def _unpack(mm: torch.Tensor, width: int, rows: int, base: int = 0) -> list:
+    """Each level a view of its own, so it can be written in place, and the padding after
+    the last need not be there."""
+    return [mm[base + off:base + off + n].view(shape)
+            for off, n, shape in _level_spans(width, rows)]
 
 
 def maxmip(h: torch.Tensor, fuse_depth: int = 0, out: torch.Tensor | None = None) -> torch.Tensor:
@@ -139,7 +135,7 @@ def bound_unpack(b: torch.Tensor, width: int, rows: int) -> list:
     """Views of levels 0..L-1 of a packed tap-bound pyramid as [rows_m, width_m] tensors."""
     out = [b[:width * rows].view(rows, width)]
     if maxmip_levels(width, rows) > 1:
-        out += _unpack(b[bound_level_offset(width, rows, 1):], width, rows)
+        out += _unpack(b, width, rows, bound_level_offset(width, rows, 1))
     return out
 
 
