@@ -9,6 +9,7 @@ import ctypes as C
 import math
 from dataclasses import dataclass
 from functools import lru_cache
+from operator import index
 
 import torch
 
@@ -54,20 +55,24 @@ class Params:
                           float(self.uniform_step), int(self.prune), int(self.ray_tile), lst)
 
 
-# The layout depends on the sizes alone, so each is asked of the library once.
-@lru_cache(maxsize=1024)
 def maxmip_levels(width: int, rows: int) -> int:
     return L.lib().ss_maxmip_levels(width, rows)
 
 
-@lru_cache(maxsize=1024)
 def maxmip_floats(width: int, rows: int) -> int:
     return L.lib().ss_maxmip_floats(width, rows)
 
 
-@lru_cache(maxsize=4096)
 def maxmip_level_offset(width: int, rows: int, level: int) -> int:
     return L.lib().ss_maxmip_level_offset(width, rows, level)
+
+
+# The layout depends on the sizes alone, so the binding asks the library once for each.  Only
+# plain ints get here: other arguments may be changed in place, or are refused above.
+@lru_cache(maxsize=1024)
+def _floats(width: int, rows: int) -> tuple:
+    """(maxmip_floats, bound_floats) of a tensor's sizes."""
+    return maxmip_floats(width, rows), bound_floats(width, rows)
 
 
 @lru_cache(maxsize=256)
@@ -84,15 +89,16 @@ def _level_spans(width: int, rows: int) -> list:
 def _unpack(mm: torch.Tensor, width: int, rows: int, base: int = 0) -> list:
     """Each level a view of its own, so it can be written in place, and the padding after
     the last need not be there."""
+    maxmip_levels(width, rows)  # refuses what the library does
     return [mm[base + off:base + off + n].view(shape)
-            for off, n, shape in _level_spans(width, rows)]
+            for off, n, shape in _level_spans(index(width), index(rows))]
 
 
 def maxmip(h: torch.Tensor, fuse_depth: int = 0, out: torch.Tensor | None = None) -> torch.Tensor:
     """Levels >= 1 of the maximum mipmap of h, packed (ss_maxmip_level_offset)."""
     _dev_f32_2d(h)
     rows, width = h.shape
-    n = max(1, maxmip_floats(width, rows))
+    n = max(1, _floats(width, rows)[0])
     if out is None:
         out = torch.empty(n, dtype=torch.float32, device=h.device)
     elif out.numel() < n or out.dtype != torch.float32 or not out.is_cuda:
@@ -107,12 +113,10 @@ def maxmip_unpack(mm: torch.Tensor, width: int, rows: int) -> list:
     return _unpack(mm, width, rows)
 
 
-@lru_cache(maxsize=1024)
 def bound_floats(width: int, rows: int) -> int:
     return L.lib().ss_bound_floats(width, rows)
 
 
-@lru_cache(maxsize=4096)
 def bound_level_offset(width: int, rows: int, level: int) -> int:
     return L.lib().ss_bound_level_offset(width, rows, level)
 
@@ -121,7 +125,7 @@ def bound_build(h: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tenso
     """Tap-bound pyramid of h (ss_bound_build), packed (ss_bound_level_offset)."""
     _dev_f32_2d(h)
     rows, width = h.shape
-    n = max(1, bound_floats(width, rows))
+    n = max(1, _floats(width, rows)[1])
     if out is None:
         out = torch.empty(n, dtype=torch.float32, device=h.device)
     elif out.numel() < n or out.dtype != torch.float32 or not out.is_cuda:
@@ -713,7 +717,7 @@ def _alloc_batch(heights, suns, outs, mms, windows=None, ws=None):
     dev = heights[0].device
     windows = windows or [None] * len(heights)
     if mms is None:
-        mms = [torch.empty(max(1, maxmip_floats(h.shape[1], h.shape[0])), dtype=torch.float32,
+        mms = [torch.empty(max(1, _floats(h.shape[1], h.shape[0])[0]), dtype=torch.float32,
                            device=dev) for h in heights]
     if outs is None:
         outs = [[torch.empty(_ray_shape(h, w), dtype=torch.float32, device=dev) for _ in suns]
@@ -735,7 +739,7 @@ def _alloc_batch(heights, suns, outs, mms, windows=None, ws=None):
 def _bounds_for(heights, params, bounds):
     """Tap-bound buffers for the exact mode (the batched call fills them)."""
     if bounds is None and params.mode == L.SS_MODE_EXACT:
-        bounds = [torch.empty(max(1, bound_floats(h.shape[1], h.shape[0])), dtype=torch.float32,
+        bounds = [torch.empty(max(1, _floats(h.shape[1], h.shape[0])[1]), dtype=torch.float32,
                               device=h.device) for h in heights]
     return bounds
 

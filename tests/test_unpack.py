@@ -1,4 +1,7 @@
 """Levels cut out of a packed pyramid (no GPU: layout and views only)."""
+import ctypes
+
+import numpy as np
 import pytest
 import torch
 
@@ -60,3 +63,30 @@ def test_levels_can_be_written_in_place():
     wide = torch.rand(2 * ss.maxmip_floats(width, rows))[::2]
     for a, c in zip(ss.maxmip_unpack(wide, width, rows), ss.maxmip_unpack(wide.clone(), width, rows)):
         assert torch.equal(a, c)
+
+
+@pytest.mark.parametrize("call", [ss.maxmip_levels, ss.maxmip_floats, ss.bound_floats,
+                                  lambda w, r: ss.maxmip_level_offset(w, r, 1),
+                                  lambda w, r: ss.bound_level_offset(w, r, 1)])
+def test_layout_of_any_integer(call):
+    """Sizes of every integer type, as they are at the call, and no floats, whatever was asked
+    before."""
+    want, other = call(300, 200), call(600, 200)
+    assert call(np.int64(300), 200) == call(np.array(300), 200) == want
+    w = torch.tensor(300)
+    assert call(w, 200) == want
+    w.fill_(600)
+    assert call(w, 200) == other
+    for bad in (300.0, "300", None, [300]):
+        with pytest.raises(ctypes.ArgumentError):
+            call(bad, 200)
+
+
+def test_unpack_of_any_integer():
+    mm = torch.rand(ss.maxmip_floats(300, 200))
+    want = ss.maxmip_unpack(mm, 300, 200)
+    for w in (np.int64(300), np.array(300), torch.tensor(300)):
+        got = ss.maxmip_unpack(mm, w, 200)
+        assert len(got) == len(want) and all(torch.equal(a, b) for a, b in zip(got, want))
+    with pytest.raises(ctypes.ArgumentError):
+        ss.maxmip_unpack(mm, 300.0, 200)
