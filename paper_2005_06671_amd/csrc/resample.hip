@@ -106,16 +106,22 @@ __global__ __launch_bounds__(256) void resample_kernel(ResampleK K) {
 // The destination texels [i0, i1) x [j0, j1) that can fall into the source: its
 // four corners seen from the destination plane.  When all lie in front of that
 // plane the source's image is the quadrilateral they span (a central projection
-// maps lines to lines), so its bounding box, a texel wider than rounding could
-// ask for, holds every covered texel; otherwise the whole tile stays.
+// maps lines to lines), so its bounding box holds every covered texel; otherwise
+// the whole tile stays.  Seen the other way round a position is off by up to
+// 5e-9 (R + E)^2 / R, E metres out in the plane, as a frame's axes need only be
+// orthogonal and of unit length within 1e-9: both the corners and the box are
+// moved out by twice that (0.1 m on the Moon), and the box by two texels.
 void covered(const ResampleK& K, int* i0, int* i1, int* j0, int* j1) {
   *i0 = *j0 = 0;
   *i1 = K.Wd;
   *j1 = K.Hd;
-  double lo[2] = {1e300, 1e300}, hi[2] = {-1e300, -1e300};
+  double lo[2] = {1e300, 1e300}, hi[2] = {-1e300, -1e300}, out = 0.0;
+  auto slack = [&](double e) { return 1e-8 * (K.R + e) * (1.0 + e / K.R); };
+  const double sx = 0.5 * K.Ws * K.Ds, sy = 0.5 * K.Hs * K.Ds;
+  const double grow = slack(fmax(fabs(K.oxs) + sx, fabs(K.oys) + sy));
   for (int c = 0; c < 4; ++c) {
-    const double X = K.oxs + ((c & 1) ? 0.5 : -0.5) * K.Ws * K.Ds;
-    const double Y = K.oys + ((c & 2) ? 0.5 : -0.5) * K.Hs * K.Ds;
+    const double X = K.oxs + ((c & 1) ? 1.0 : -1.0) * (sx + grow);
+    const double Y = K.oys + ((c & 2) ? 1.0 : -1.0) * (sy + grow);
     double P[3], z = 0.0, x = 0.0, y = 0.0;
     for (int k = 0; k < 3; ++k) {
       P[k] = K.R * K.cs[k] + X * K.exs[k] + Y * K.eys[k];
@@ -124,18 +130,22 @@ void covered(const ResampleK& K, int* i0, int* i1, int* j0, int* j1) {
       y += P[k] * K.eyd[k];
     }
     if (!(z > 1e-3 * K.R)) return;
-    const double q[2] = {(x * (K.R / z) - K.oxd) / K.Dd + 0.5 * K.Wd,
-                         (y * (K.R / z) - K.oyd) / K.Dd + 0.5 * K.Hd};
+    x *= K.R / z;
+    y *= K.R / z;
+    out = fmax(out, fmax(fabs(x), fabs(y)));
+    const double q[2] = {(x - K.oxd) / K.Dd + 0.5 * K.Wd, (y - K.oyd) / K.Dd + 0.5 * K.Hd};
+    if (!isfinite(q[0]) || !isfinite(q[1])) return;
     for (int a = 0; a < 2; ++a) {
       lo[a] = fmin(lo[a], q[a]);
       hi[a] = fmax(hi[a], q[a]);
     }
   }
   if (!(hi[0] - lo[0] < 1e9 && hi[1] - lo[1] < 1e9)) return;
-  *i0 = (int)fmin(fmax(floor(lo[0]) - 2.0, 0.0), (double)K.Wd);
-  *i1 = (int)fmin(fmax(ceil(hi[0]) + 2.0, 0.0), (double)K.Wd);
-  *j0 = (int)fmin(fmax(floor(lo[1]) - 2.0, 0.0), (double)K.Hd);
-  *j1 = (int)fmin(fmax(ceil(hi[1]) + 2.0, 0.0), (double)K.Hd);
+  const double pad = 2.0 + slack(out) / K.Dd;
+  *i0 = (int)fmin(fmax(floor(lo[0] - pad), 0.0), (double)K.Wd);
+  *i1 = (int)fmin(fmax(ceil(hi[0] + pad), 0.0), (double)K.Wd);
+  *j0 = (int)fmin(fmax(floor(lo[1] - pad), 0.0), (double)K.Hd);
+  *j1 = (int)fmin(fmax(ceil(hi[1] + pad), 0.0), (double)K.Hd);
 }
 
 bool ordinary(double v) { return fabs(v) > 1e-60 && fabs(v) < 1e60; }
