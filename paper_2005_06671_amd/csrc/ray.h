@@ -16,12 +16,22 @@
 
 #define SS_INF __builtin_inff()
 
-// Kernels that trace rays: 256 threads, held to 7 wavefronts per SIMD (72 VGPRs).
-// The descent is bound by instruction issue and gathers together, so wavefronts
-// in flight count: the 8 suns of a 4096^2 tile take 7.64 ms at the 6 its free
-// allocation (84) gives, 6.76 at 7 and 7.04 at 8, which spills in the levels.
-#define SS_RAY_KERNEL \
-  __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(7)))
+// Kernels that trace rays: 256 threads, held to `waves` wavefronts per SIMD.  The
+// descent is bound by instruction issue and gathers together, so wavefronts in flight
+// count: the 8 suns of a 4096^2 tile take 7.64 ms at the 6 its free allocation (84
+// VGPRs) gives, 6.76 at 7 (72, 24 bytes of them in scratch) and 7.04 at 8, which spills
+// in the levels.
+//
+// Kernels that hold more than a descent lose by the spills what a seventh wavefront
+// gives.  us at 7 / 6 wavefronts: the exact mode, 1024^2 tiles at 1.5 deg 213 / 205 and
+// at another azimuth 267 / 236, 512^2 151 / 138, 2048^2 1027 / 1033; the adjoint, 1024^2
+// replaying 81 / 75, from a record 25.6 / 24.5, 2048^2 in the penumbra 290 / 283 (left
+// to itself the allocation takes 97 to 121 VGPRs there, 4 wavefronts, and the 2048^2
+// replay takes 365 where it takes 320 at 6).  The points' adjoint at 7 / 6 / 5 / 4: a
+// 512 x 384 image 46.3 / 42.4 / 34.4 / 33.3, 1920 x 1080 201 / 203 / 194 / 215.
+#define SS_RAY_KERNEL_AT(waves) \
+  __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(waves)))
+#define SS_RAY_KERNEL SS_RAY_KERNEL_AT(7)
 
 // Workgroup ids are dealt round-robin over the 8 XCDs.  xcd_remap gives each
 // XCD one contiguous run of [0, nb) (the first nb % 8 XCDs one id more);

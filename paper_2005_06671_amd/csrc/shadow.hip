@@ -48,10 +48,9 @@ __device__ __forceinline__ void ray_coords(int nbx, int nblocks, int grp, int& i
 enum { FWD_PLAIN = 0, FWD_COUNT = 1, FWD_SAVE = 2 };
 
 template <bool SPHERE, int TW, int MODE, int FLAGS>
-SS_RAY_KERNEL void shadow_kernel(TileK T, float* __restrict__ out,
-                                                     unsigned long long* counter,
-                                                     int* __restrict__ sample, int nbx,
-                                                     int nblocks) {
+SS_RAY_KERNEL_AT(MODE == SS_MODE_EXACT ? 6 : 7)
+void shadow_kernel(TileK T, float* __restrict__ out, unsigned long long* counter,
+                   int* __restrict__ sample, int nbx, int nblocks) {
   constexpr bool COUNT = FLAGS == FWD_COUNT;
   __shared__ int tab[SS_MAXLEV];
   if (MODE == SS_MODE_EXACT) {
@@ -256,7 +255,10 @@ __device__ __forceinline__ void adjoint_ray(const TileK& T, const SunTrig& st, i
     }
     const float hp = T.h[j * T.W + i];
     Ray<SPHERE> r;
-    ray_init(T, i, j, hp, r);
+    if (SAVED)  // most of the kernel: one form of the set-up, 23.7 us a 1024^2 tile for 24.3
+      ray_init_as<SPHERE, false>(T, i, j, hp, r, -0.0f, -0.0f, -0.0f);
+    else
+      ray_init(T, i, j, hp, r);
     RayResult res;
     if (SAVED) {
       // the recorded sample, with the forward's own arithmetic: t rounded once
@@ -298,13 +300,10 @@ struct AdjBlocks {
 };
 
 template <bool SPHERE, int TW, int MODE, bool SAVED>
-SS_RAY_KERNEL void adjoint_kernel(TileK T, SunTrig st,
-                                                      const float* __restrict__ gs,
-                                                      const int* __restrict__ sample,
-                                                      const float* __restrict__ sfwd,
-                                                      float* __restrict__ gh,
-                                                      double* __restrict__ gsun, int nbx,
-                                                      int nblocks) {
+SS_RAY_KERNEL_AT(6)
+void adjoint_kernel(TileK T, SunTrig st, const float* __restrict__ gs,
+                    const int* __restrict__ sample, const float* __restrict__ sfwd,
+                    float* __restrict__ gh, double* __restrict__ gsun, int nbx, int nblocks) {
   __shared__ double red[2][4];
   __shared__ int tab[SS_MAXLEV];
   if (MODE == SS_MODE_EXACT && !SAVED) {
@@ -350,12 +349,10 @@ SS_RAY_KERNEL void adjoint_kernel(TileK T, SunTrig st,
 #define SS_PEN_BLOCKS 8
 
 template <bool SPHERE, int MODE>
-SS_RAY_KERNEL void adjoint_penumbra_kernel(TileK T, SunTrig st,
-                                                               const float* __restrict__ gs,
-                                                               const float* __restrict__ sfwd,
-                                                               float* __restrict__ gh,
-                                                               double* __restrict__ gsun, int nbx,
-                                                               int nblocks) {
+SS_RAY_KERNEL_AT(6)
+void adjoint_penumbra_kernel(TileK T, SunTrig st, const float* __restrict__ gs,
+                             const float* __restrict__ sfwd, float* __restrict__ gh,
+                             double* __restrict__ gsun, int nbx, int nblocks) {
   __shared__ double red[2][4];
   __shared__ int tab[SS_MAXLEV];
   __shared__ unsigned list[SS_PEN_BLOCKS * 256];
@@ -434,9 +431,9 @@ __device__ __forceinline__ float shade_point(const TileK& T, float2 q, const int
 // neighbours on the terrain, so their shadow rays walk the same cells (a row
 // of 64 pixels spreads them out).  Otherwise lane k takes point k.
 template <bool SPHERE, int MODE, bool IMAGE>
-SS_RAY_KERNEL void points_kernel(TileK T, const float2* __restrict__ xy,
-                                                     long long n, int img_w, int nbx,
-                                                     float* __restrict__ out) {
+SS_RAY_KERNEL_AT(MODE == SS_MODE_EXACT ? 6 : 7)
+void points_kernel(TileK T, const float2* __restrict__ xy, long long n, int img_w, int nbx,
+                   float* __restrict__ out) {
   __shared__ int tab[SS_MAXLEV];
   if (MODE == SS_MODE_EXACT) {
     bound_tab_fill(T, tab);
@@ -463,12 +460,10 @@ SS_RAY_KERNEL void points_kernel(TileK T, const float2* __restrict__ xy,
 // Work is mapped as in points_kernel; the sun gradient is reduced per
 // workgroup as in adjoint_kernel.
 template <bool SPHERE, int MODE, bool IMAGE>
-SS_RAY_KERNEL void points_adjoint_kernel(TileK T, SunTrig st,
-                                                             const float2* __restrict__ xy,
-                                                             long long n, int img_w, int nbx,
-                                                             const float* __restrict__ gs,
-                                                             float* __restrict__ gh,
-                                                             double* __restrict__ gsun) {
+SS_RAY_KERNEL_AT(5)
+void points_adjoint_kernel(TileK T, SunTrig st, const float2* __restrict__ xy, long long n,
+                           int img_w, int nbx, const float* __restrict__ gs,
+                           float* __restrict__ gh, double* __restrict__ gsun) {
   __shared__ double red[2][4];
   __shared__ int tab[SS_MAXLEV];
   if (MODE == SS_MODE_EXACT) {
