@@ -339,12 +339,26 @@ static int32_t make_tilek(const ss_tile* t, const ss_sun* s, const Resolved& rp,
 //     19.2 / 15.1, 1024^2 at 75 37.8 / 44.8, 256^2 at 45 21.2 / 20.8, at 75 16.5 /
 //     13.2; exact: 1024^2 at 20 deg 190 / 223, at 45 89 / 73, at 75 60 / 50, 512^2 at
 //     20 137 / 140, at 75 29 / 23.
+// The exact mode's rays step together to pass over terrain, where its walk lets each go
+// its own way.  That does not pay for a list of points, whose rays may start anywhere
+// (196608 scattered points 357 us together, 210 by the walk; an image's rays start
+// beside each other, 240 x 320 points two texels apart 210 / 284, sixteen apart 446 /
+// 564), nor up to 2^20 rays for wide ray tiles (1024^2 in 32 x 2 ray tiles 320 / 284,
+// 295 / 249 and 359 / 317 at three azimuths; 2048^2 1285 / 1195, 1092 / 1334 and 1568 /
+// 1922) and adjoints (1024^2 in the penumbra 230 / 200, a 512 x 384 image 231 / 201;
+// 2048^2 874 / 950, 1920 x 1080 794 / 906).
 // rays: how many step.
-static int32_t know_heights(TileK* K, const Resolved& rp, int64_t rays, hipStream_t stream) {
+enum class Rays { tile, adjoint, image, image_adjoint, list };
+
+static int32_t know_heights(TileK* K, const Resolved& rp, Rays kind, int64_t rays,
+                            hipStream_t stream) {
   const bool exact = rp.mode == SS_MODE_EXACT;
   if ((rp.mode != SS_MODE_UNIFORM && !exact) || !rp.prune || K->L < 2) return SS_OK;
   const bool steep = exact ? K->Lz > 0.5f : K->Lz > 0.87f && rays < (1 << 19);
-  if (steep || rays < ((int64_t)K->W * K->H + 63) / 64) {
+  const bool wide = kind == Rays::tile && (rp.ray_tile == SS_TILE_16x4 || rp.ray_tile == SS_TILE_32x2);
+  const bool apart = kind == Rays::list ||
+                     (rays <= (1 << 20) && (wide || kind == Rays::adjoint || kind == Rays::image_adjoint));
+  if (steep || (exact && apart) || rays < ((int64_t)K->W * K->H + 63) / 64) {
     K->prune = 2;
     return SS_OK;
   }
@@ -365,7 +379,8 @@ static int32_t cast_common(const ss_tile* tile, const ss_sun* sun, const ss_para
   TileK K;
   if ((rc = make_tilek(tile, sun, rp, params->max_len_m, params->body_radius_m, &K))) return rc;
   if (!d_sample &&
-      (rc = know_heights(&K, rp, (int64_t)K.RW * K.RH, (hipStream_t)stream))) return rc;
+      (rc = know_heights(&K, rp, Rays::tile, (int64_t)K.RW * K.RH, (hipStream_t)stream)))
+    return rc;
   SS_HIP(launch_forward(K, rp.sphere, rp.mode, rp.ray_tile, counter != nullptr, d_shadow, counter,
                         d_sample, (hipStream_t)stream));
   return SS_OK;
@@ -405,7 +420,8 @@ static int32_t backward_common(const ss_tile* tile, const ss_sun* sun, const ss_
   TileK K;
   if ((rc = make_tilek(tile, sun, rp, params->max_len_m, params->body_radius_m, &K))) return rc;
   if (!d_sample &&
-      (rc = know_heights(&K, rp, (int64_t)K.RW * K.RH, (hipStream_t)stream))) return rc;
+      (rc = know_heights(&K, rp, Rays::adjoint, (int64_t)K.RW * K.RH, (hipStream_t)stream)))
+    return rc;
   SS_HIP(launch_adjoint(K, rp.sphere, rp.mode, sun->elev_rad, sun->azim_rad, d_grad_shadow,
                         d_sample, d_shadow, d_grad_height, d_grad_sun, (hipStream_t)stream));
   return SS_OK;
@@ -424,7 +440,7 @@ extern "C" int32_t ss_shadow_points(const ss_tile* tile, const ss_sun* sun,
   if ((reinterpret_cast<uintptr_t>(d_xy) & 7) != 0) return SS_ERR_INVALID_ARG;
   TileK K;
   if ((rc = make_tilek(tile, sun, rp, params->max_len_m, params->body_radius_m, &K))) return rc;
-  if ((rc = know_heights(&K, rp, n, (hipStream_t)stream))) return rc;
+  if ((rc = know_heights(&K, rp, Rays::list, n, (hipStream_t)stream))) return rc;
   SS_HIP(launch_points(K, rp.sphere, rp.mode, d_xy, n, 0, d_shadow, (hipStream_t)stream));
   return SS_OK;
 }
@@ -448,7 +464,9 @@ extern "C" int32_t ss_shadow_points_backward(const ss_tile* tile, const ss_sun* 
   if ((reinterpret_cast<uintptr_t>(d_grad_sun) & 7) != 0) return SS_ERR_INVALID_ARG;
   TileK K;
   if ((rc = make_tilek(tile, sun, rp, params->max_len_m, params->body_radius_m, &K))) return rc;
-  if ((rc = know_heights(&K, rp, n, (hipStream_t)stream))) return rc;
+  if ((rc = know_heights(&K, rp, width > 0 ? Rays::image_adjoint : Rays::list, n,
+                         (hipStream_t)stream)))
+    return rc;
   SS_HIP(launch_points_adjoint(K, rp.sphere, rp.mode, sun->elev_rad, sun->azim_rad, d_xy, n, width,
                                d_grad_shadow, d_grad_height, d_grad_sun, (hipStream_t)stream));
   return SS_OK;
@@ -468,7 +486,8 @@ extern "C" int32_t ss_shadow_points_image(const ss_tile* tile, const ss_sun* sun
   if ((reinterpret_cast<uintptr_t>(d_xy) & 7) != 0) return SS_ERR_INVALID_ARG;
   TileK K;
   if ((rc = make_tilek(tile, sun, rp, params->max_len_m, params->body_radius_m, &K))) return rc;
-  if ((rc = know_heights(&K, rp, (int64_t)width * height, (hipStream_t)stream))) return rc;
+  if ((rc = know_heights(&K, rp, Rays::image, (int64_t)width * height, (hipStream_t)stream)))
+    return rc;
   SS_HIP(launch_points(K, rp.sphere, rp.mode, d_xy, (long long)width * height, width, d_shadow,
                        (hipStream_t)stream));
   return SS_OK;

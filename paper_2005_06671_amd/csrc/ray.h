@@ -1235,18 +1235,21 @@ __device__ __forceinline__ float bound_at(const TileK& T, const int* tab, int m,
 // bit-identical to uniform stepping at half a texel (prune = 0 evaluates
 // every sample).
 //
-// That walk is for tiles with missing or infinite heights, for prune = 0 and for the
-// forward that records the deciding sample (KEEP).  Otherwise the wavefront's rays step
-// through the grid together (step_through): 64 lanes at levels and samples of their own
-// run every branch of an iteration, so the walk took as long as its slowest ray at 130
-// instructions an iteration, mostly waiting for one gather.  Same results; 2048^2 tiles
-// at 1.5 deg, 0.2 deg: 912 to 1153 us and 2700 with the walk, 826 to 1022 and 1955 now.
+// That walk is for tiles with missing or infinite heights, for prune = 0, for the
+// forward that records the deciding sample (KEEP), for rays that may start anywhere
+// (NEAR false) and where the host has found that it costs less (know_heights).
+// Otherwise the wavefront's rays step through the grid together (step_through): 64
+// lanes at levels and samples of their own run every branch of an iteration, so the
+// walk takes as long as its slowest ray at 130 instructions an iteration, mostly
+// waiting for one gather.  Same results; us with the walk / stepping, 2048^2 tiles at
+// 0.2 deg 6332 / 4385, at 1.5 deg in 4 x 16 ray tiles 902 to 1446 / 704 to 1101 over
+// four azimuths, 1024^2 in 8 x 8 ray tiles 218 to 264 / 203 to 286.
 //
 // Branch and bound prunes best with a good incumbent: the descent (Sec. 3.2)
 // runs first and its deciding sample, a sample of the same grid computed by
 // the same arithmetic, seeds the minimum when it lies within the cap.  A ray
 // the descent already finds in umbra is then done.
-template <bool SPHERE, bool KEEP>
+template <bool SPHERE, bool KEEP, bool NEAR>
 __device__ __forceinline__ RayResult shadow_exact(const TileK& T, const Ray<SPHERE>& r, float top,
                                                   unsigned& n_tst, unsigned& n_smp,
                                                   const int* tab) {
@@ -1266,7 +1269,7 @@ __device__ __forceinline__ RayResult shadow_exact(const TileK& T, const Ray<SPHE
       best = d.key;
     }
   }
-  if (!KEEP && T.prune == 1 && heights_finite(T)) {
+  if (!KEEP && NEAR && T.prune == 1 && heights_finite(T)) {
     res.key = best;
     step_through(T, r, top, T.half_delta, chunk_level(0.5), true, res, n_smp);
     return res;
@@ -1343,12 +1346,12 @@ __device__ __forceinline__ float terrain_top(const TileK& T, const Ray<SPHERE>& 
 }
 
 // The shadow clearance of one ray by the chosen method.  KEEP: for a caller that hands
-// out the deciding sample.
-template <bool SPHERE, int MODE, bool KEEP = false>
+// out the deciding sample.  NEAR: the wavefront's rays start beside each other.
+template <bool SPHERE, int MODE, bool KEEP = false, bool NEAR = true>
 __device__ __forceinline__ RayResult trace_ray(const TileK& T, const Ray<SPHERE>& r, unsigned& n_lb,
                                                unsigned& n_smp, const int* tab) {
   const float top = terrain_top(T, r);
-  if (MODE == SS_MODE_EXACT) return shadow_exact<SPHERE, KEEP>(T, r, top, n_lb, n_smp, tab);
+  if (MODE == SS_MODE_EXACT) return shadow_exact<SPHERE, KEEP, NEAR>(T, r, top, n_lb, n_smp, tab);
   if (MODE == SS_MODE_POINT) return shadow_dp<SPHERE, true>(T, r, top, n_lb, n_smp);
   if (MODE == SS_MODE_UNIFORM) return shadow_uniform<SPHERE, KEEP>(T, r, top, n_smp);
   return shadow_dp<SPHERE, false, KEEP>(T, r, top, n_lb, n_smp);

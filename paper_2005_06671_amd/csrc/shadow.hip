@@ -412,7 +412,7 @@ void adjoint_penumbra_kernel(TileK T, SunTrig st, const float* __restrict__ gs,
 
 // Shadow rays from arbitrary surface points: point k at continuous texel
 // coordinates xy[k] (clamped to the tile), on the bilinear terrain there.
-template <bool SPHERE, int MODE>
+template <bool SPHERE, int MODE, bool NEAR>
 __device__ __forceinline__ float shade_point(const TileK& T, float2 q, const int* tab) {
   if (q.x != q.x || q.y != q.y) return NAN;  // a view ray's miss: nothing to shade
   const float qx = fminf(fmaxf(q.x, 0.0f), (float)T.W), qy = fminf(fmaxf(q.y, 0.0f), (float)T.H);
@@ -423,7 +423,7 @@ __device__ __forceinline__ float shade_point(const TileK& T, float2 q, const int
   ray_init(T, i, j, ref, r, qx - ((float)i + 0.5f), qy - ((float)j + 0.5f),
            terrain_above(T, qx, qy, ref));
   unsigned n_lb = 0, n_smp = 0;
-  return disc_fraction(trace_ray<SPHERE, MODE>(T, r, n_lb, n_smp, tab).alpha, T);
+  return disc_fraction(trace_ray<SPHERE, MODE, false, NEAR>(T, r, n_lb, n_smp, tab).alpha, T);
 }
 
 // IMAGE: the points form an image [n / img_w][img_w] and a wavefront takes an
@@ -451,7 +451,7 @@ void points_kernel(TileK T, const float2* __restrict__ xy, long long n, int img_
     k = (long long)blockIdx.x * 256 + threadIdx.x;
   }
   if (k >= n) return;
-  out[k] = shade_point<SPHERE, MODE>(T, xy[k], tab);
+  out[k] = shade_point<SPHERE, MODE, IMAGE>(T, xy[k], tab);
 }
 
 // Adjoint of shadow rays from surface points, the points held fixed: the
@@ -497,7 +497,7 @@ void points_adjoint_kernel(TileK T, SunTrig st, const float2* __restrict__ xy, l
       Ray<SPHERE> r;
       ray_init(T, i, j, ref, r, ox, oy, dz);
       unsigned n_lb = 0, n_smp = 0;
-      const RayResult res = trace_ray<SPHERE, MODE>(T, r, n_lb, n_smp, tab);
+      const RayResult res = trace_ray<SPHERE, MODE, false, IMAGE>(T, r, n_lb, n_smp, tab);
       float X = 0.0f, Y = 0.0f;
       if (SPHERE) {
         X = ((float)i + 0.5f + ox - 0.5f * (float)T.W) * T.texel;
