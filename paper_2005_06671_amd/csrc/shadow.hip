@@ -652,10 +652,15 @@ void grid_for(const TileK& T, int ray_tile, int* nbx, int* nblocks) {
 // (T.wg_group / 2 SIMDs on the device).  us per launch, whole / split, on square
 // tiles: 96: 13.4 / 7.1, 256: 19.0 / 11.8, 320: 21.1 / 13.4, 384 (2.3 wavefronts):
 // 22.0 / 18.4, 448 (3.1): 23.9 / 24.1, 512: 27.6 / 31.0; point samples 256: 10.7 / 7.1,
-// 384: 14.0 / 12.2, 448: 16.3 / 15.7, 512: 17.2 / 18.9.
+// 384: 14.0 / 12.2, 448: 16.3 / 15.7, 512: 17.2 / 18.9.  And suns up to 60 deg: above,
+// most rays clear the terrain within their first run and three of the wavefronts have
+// nothing to do (with the events' own time, 45 deg: 256: 14.3 / 12.0, 384: 17.3 / 17.4;
+// 60 deg: 12.6 / 11.6 and 14.6 / 17.1; 75 deg: 10.7 / 11.6 and 13.6 / 16.6; 85 deg: 10.6
+// / 11.3 and 11.7 / 16.4).
 static bool split_pays(const TileK& T, int mode, int flags, int ray_tile, int nb) {
   return (mode == SS_MODE_DP || mode == SS_MODE_POINT) && flags == FWD_PLAIN &&
-         ray_tile == SS_TILE_8x8 && T.nseg > 1 && 8LL * nb <= 5LL * (T.wg_group / 2);
+         ray_tile == SS_TILE_8x8 && T.nseg > 1 && T.Lz <= 0.87f &&
+         8LL * nb <= 5LL * (T.wg_group / 2);
 }
 
 template <bool SPHERE>
