@@ -238,8 +238,9 @@ static int device_wg_group() {
   return v;
 }
 
+// batch: a pair of the batched call, whose fits' error bounds the expand kernel forms.
 static int32_t make_tilek(const ss_tile* t, const ss_sun* s, const Resolved& rp, double max_len_m,
-                          double radius, TileK* K) {
+                          double radius, TileK* K, bool batch = false) {
   memset(K, 0, sizeof(*K));
   K->wg_group = device_wg_group();
   const int W = t->width, H = t->rows;
@@ -306,9 +307,11 @@ static int32_t make_tilek(const ss_tile* t, const ss_sun* s, const Resolved& rp,
   }
   K->nseg = j;
   K->tau[j] = run_start_len(ga, half_delta);
+  const int fits = rp.mode == SS_MODE_DP || rp.mode == SS_MODE_EXACT ? j : 0;  // the descents
   for (int k = 0; k < SS_FITRUNS; ++k)
-    K->fit_err[k] = k < j ? run_fit_err(W, H, K->texel, K->invR, K->Lz, half_delta, K->run[k])
-                          : SS_FIT_NONE;
+    K->fit_err[k] = k >= fits ? SS_FIT_NONE
+                    : batch   ? 0u
+                              : run_fit_err(W, H, K->texel, K->invR, K->Lz, half_delta, K->run[k]);
   const double tau = (double)(ga + 1) * half_delta;
   // uniform steps stop at the cap, or without one at the tile edge and at the
   // latest after the runs' extent (the tile diagonal)
@@ -746,7 +749,7 @@ static int32_t build_image(const ss_tile* tiles, int32_t n_tiles, const ss_sun* 
       const size_t p = (size_t)t * n_suns + k;
       TileK K;
       if ((rc = make_tilek(&tiles[t], &suns[k], bi->rp, params->max_len_m, params->body_radius_m,
-                           &K)))
+                           &K, true)))
         return rc;
       if (k == 0) {
         bi->tmpl[t] = K;

@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64) void expand_kernel(const TileK* __restrict__ tm
       const int a = j < nseg ? run_a0(T.run[j])
                              : run_a0(T.run[nseg - 1]) + (2 << run_m0(T.run[nseg - 1]));
       v = __float_as_uint(run_start_len(a, P.half_delta));
-    } else if (w >= W_ERR && w < W_ERR + SS_FITRUNS && w - W_ERR < nseg) {
+    } else if (w >= W_ERR && w < W_ERR + SS_FITRUNS && v != SS_FIT_NONE) {
       v = run_fit_err(T.W, T.H, T.texel, T.invR, P.sun[2], P.half_delta, T.run[w - W_ERR]);
     }
     dst[w] = v;
