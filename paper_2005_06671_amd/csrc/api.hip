@@ -80,9 +80,10 @@ extern "C" int64_t ss_maxmip_floats(int32_t width, int32_t rows) {
   return ss_maxmip_level_offset(width, rows, levels_of(width, rows));
 }
 
-// from: levels up to this one are there already.
+// check: with the word on finite heights, for calls that step.  from: levels up to this
+// one are there already (of the tap-bound pyramid, which has no such word).
 static int32_t maxmip_build(const float* d_height, int32_t W, int32_t H, float* d_mm, int fuse,
-                            hipStream_t stream, int from = 0) {
+                            bool check, hipStream_t stream, int from = 0) {
   const int L = levels_of(W, H);
   if (fuse < 1 || fuse > 6) fuse = 6;
   int src_m = from;
@@ -102,8 +103,8 @@ static int32_t maxmip_build(const float* d_height, int32_t W, int32_t H, float* 
       dims_of(W, H, src_m - 1, &bw, &bh);
       below = src_m == 1 ? d_height : d_mm + ss_maxmip_level_offset(W, H, src_m - 1);
     }
-    SS_HIP(launch_maxmip(src, sw, sh, d_mm, off, w, h, F, below, bw, bh, src_m + F == L - 1,
-                         finite_key(W, H), stream));
+    SS_HIP(launch_maxmip(src, sw, sh, d_mm, off, w, h, F, below, bw, bh,
+                         from == 0 && src_m + F == L - 1, finite_key(W, H), check, stream));
     src_m += F;
   }
   return SS_OK;
@@ -115,7 +116,7 @@ extern "C" int32_t ss_maxmip_build(const float* d_height, int32_t width, int32_t
   if (!size_ok(width, rows) || !d_height) return SS_ERR_INVALID_ARG;
   if (fuse_depth < 0 || fuse_depth > 6) return SS_ERR_INVALID_ARG;
   if (ss_maxmip_floats(width, rows) > 0 && !d_maxmip) return SS_ERR_INVALID_ARG;
-  return maxmip_build(d_height, width, rows, d_maxmip, fuse_depth ? fuse_depth : 6,
+  return maxmip_build(d_height, width, rows, d_maxmip, fuse_depth ? fuse_depth : 6, true,
                       (hipStream_t)stream);
 }
 
@@ -151,7 +152,7 @@ extern "C" int32_t ss_bound_build(const float* d_height, int32_t width, int32_t 
     dims_of(width, rows, 1 + k, &w[k], &h[k]);
   }
   SS_HIP(launch_bound(d_height, width, rows, d_bound, mm, off, w, h, F, s));
-  return maxmip_build(d_bound, width, rows, mm, 6, s, F);
+  return maxmip_build(d_bound, width, rows, mm, 6, false, s, F);
 }
 
 // ------------------------------------------------------------------------
@@ -196,6 +197,8 @@ static int32_t resolve_params(const ss_params* p, Resolved* r) {
   r->sphere = !isinf(p->body_radius_m);
   return SS_OK;
 }
+
+static bool steps(int mode) { return mode == SS_MODE_UNIFORM || mode == SS_MODE_EXACT; }
 
 static int32_t check_tile(const ss_tile* t, int mode) {
   if (!t) return SS_ERR_INVALID_ARG;
@@ -356,7 +359,7 @@ enum class Rays { tile, adjoint, image, image_adjoint, list };
 static int32_t know_heights(TileK* K, const Resolved& rp, Rays kind, int64_t rays,
                             hipStream_t stream) {
   const bool exact = rp.mode == SS_MODE_EXACT;
-  if ((rp.mode != SS_MODE_UNIFORM && !exact) || !rp.prune || K->L < 2) return SS_OK;
+  if (!steps(rp.mode) || !rp.prune || K->L < 2) return SS_OK;
   const bool steep = exact ? K->Lz > 0.5f : K->Lz > 0.87f && rays < (1 << 19);
   const bool wide = kind == Rays::tile && (rp.ray_tile == SS_TILE_16x4 || rp.ray_tile == SS_TILE_32x2);
   const bool apart = kind == Rays::list ||
@@ -843,7 +846,7 @@ static int32_t enqueue_batch(const ss_tile* tiles, int32_t n_tiles, const BatchD
   ws_layout(n_tiles, bd.n_suns, &L);
   for (int t = 0; t < n_tiles; ++t) {
     int32_t rc = maxmip_build(tiles[t].height, tiles[t].width, tiles[t].rows, tiles[t].maxmip,
-                              fuse, stream);
+                              fuse, steps(rp.mode), stream);
     if (rc) return rc;
     // the exact mode also reads each tile's tap-bound pyramid (sun-independent)
     if (rp.mode == SS_MODE_EXACT &&
@@ -1045,7 +1048,7 @@ static int32_t tune(const ss_tile* tiles, int n_tiles, const ss_sun* suns, int n
     for (int rep = 0; rep < 3; ++rep) {
       SS_HIP(hipEventRecord(a, s));
       int32_t rc = maxmip_build(tiles[big].height, tiles[big].width, tiles[big].rows,
-                                tiles[big].maxmip, f, s);
+                                tiles[big].maxmip, f, steps(params->mode), s);
       if (rc) return rc;
       SS_HIP(hipEventRecord(b, s));
       double ms = 0.0;
@@ -1112,7 +1115,8 @@ extern "C" int32_t ss_batched_plan_create(const ss_tile* tiles, int32_t n_tiles,
   resolve_params(params, &rp);
   // tune (mipmaps and tap-bound pyramids first: the ray kernels read them)
   for (int t = 0; t < n_tiles; ++t) {
-    rc = maxmip_build(tiles[t].height, tiles[t].width, tiles[t].rows, tiles[t].maxmip, 6, s);
+    rc = maxmip_build(tiles[t].height, tiles[t].width, tiles[t].rows, tiles[t].maxmip, 6,
+                      steps(rp.mode), s);
     if (rc) return rc;
     if (rp.mode == SS_MODE_EXACT &&
         (rc = ss_bound_build(tiles[t].height, tiles[t].width, tiles[t].rows, tiles[t].bound, s)))

@@ -10,11 +10,11 @@ namespace ss {
 #define SS_NXCD 8         // XCDs; workgroup ids are dealt round-robin over them
 
 // Maximum mipmap: levels [m_src+1, m_src+F] from level m_src (F <= 6).  below: level
-// m_src - 1 (bw x bh; nullptr when m_src is 0); last: the top is among them; key:
-// finite_key of the tile.
+// m_src - 1 (bw x bh; nullptr when m_src is 0); last: the top is among them and gets
+// its word on finite heights; key: finite_key of the tile; check: with the answer.
 hipError_t launch_maxmip(const float* src, int sw, int sh, float* dst_base, const int* dst_off,
                          const int* dst_w, const int* dst_h, int F, const float* below, int bw,
-                         int bh, int last, unsigned key, hipStream_t stream);
+                         int bh, int last, unsigned key, bool check, hipStream_t stream);
 
 // Takes back the word on finite heights beside the mipmap's top (finite_word) where the
 // tile holds a height that is missing or infinite by now.

@@ -15,7 +15,9 @@
 // reads such a texel puts its maximum back from the level below.  No other workgroup
 // reads it, so this takes no further launch, memory or pass: 16 multiply-adds a thread,
 // and a barrier where fewer than five levels are written (a 4096^2 tile's first launch
-// 16.5 us before and 17.2 with it; both launches of a 256^2 tile 5.8 and 6.4).
+// 16.5 us before and 17.2 with it; both launches of a 256^2 tile 5.8 and 6.4).  Builds
+// that no stepping follows (a batch of descents, the tap-bound pyramid) leave it out and
+// say "not known": 40 tiles of 64^2 in a batch 2.5 us each for 2.8.
 #include "kernels.h"
 #include "ray.h"
 
@@ -40,9 +42,10 @@ __device__ __forceinline__ float from_lane(float v) {
 }
 
 // Writes F levels of one 64 x 64 block from its texels v (a 4 x 4 patch a thread,
-// -inf where there is none).  CHECK: with the answer on finite heights; mine: this
-// thread has seen another.
-template <bool CHECK>
+// -inf where there is none).  CHECK: with the answer on finite heights, where mine says
+// that this thread has seen another.  WORD: the top gets its word, "not known" without
+// CHECK (the tap-bound pyramid has none).
+template <bool CHECK, bool WORD>
 __device__ __forceinline__ void block_levels(int F, const float (&v)[4][4], bool mine, float* dst,
                                              const MipDst& d, int bx, int by, float (&lds)[4][4],
                                              int (&lds_bad)[4]) {
@@ -63,9 +66,9 @@ __device__ __forceinline__ void block_levels(int F, const float (&v)[4][4], bool
     mark = bad && !d.last ? __builtin_nanf("") : 0.0f;
   };
   auto verdict = [&](float top) {
-    if (CHECK && d.last)
-      reinterpret_cast<unsigned*>(dst)[d.off[F - 1] + 1] = bad ? ~finite_word(top, d.key)
-                                                               : finite_word(top, d.key);
+    if (WORD && d.last)
+      reinterpret_cast<unsigned*>(dst)[d.off[F - 1] + 1] =
+          !CHECK || bad ? ~finite_word(top, d.key) : finite_word(top, d.key);
   };
   if (CHECK && F < 5) gather();
   // level +1: 2 x 2 per thread
@@ -152,7 +155,7 @@ __device__ __forceinline__ void block_levels(int F, const float (&v)[4][4], bool
   }
 }
 
-template <int F>
+template <int F, bool CHECK>
 __global__ __launch_bounds__(256) void maxmip_kernel(const float* src, int sw, int sh, float* dst,
                                                      MipDst d, int nbx, int vec_ok) {
   __shared__ float lds[4][4];
@@ -188,7 +191,7 @@ __global__ __launch_bounds__(256) void maxmip_kernel(const float* src, int sw, i
       }
     }
   }
-  const bool mine = !((zero[0] + zero[1]) + (zero[2] + zero[3]) == 0.0f);
+  const bool mine = CHECK && !((zero[0] + zero[1]) + (zero[2] + zero[3]) == 0.0f);
   if (mine && d.below) {
     for (int k = 0; k < 16; ++k) {
       const int y = row0 + (k >> 2), x = col0 + (k & 3);
@@ -202,7 +205,7 @@ __global__ __launch_bounds__(256) void maxmip_kernel(const float* src, int sw, i
       }
     }
   }
-  block_levels<true>(F, v, mine, dst, d, bx, by, lds, lds_bad);
+  block_levels<CHECK, true>(F, v, mine, dst, d, bx, by, lds, lds_bad);
 }
 
 // Tap-bound level 0: the maximum over the 3 x 3 block around each texel, clipped to
@@ -289,7 +292,7 @@ __global__ __launch_bounds__(256) void bound_kernel(const float* __restrict__ sr
       }
     }
   }
-  if (F > 0) block_levels<false>(F, v, false, dst, d, bx, by, lds, unused);
+  if (F > 0) block_levels<false, false>(F, v, false, dst, d, bx, by, lds, unused);
 }
 
 hipError_t launch_bound(const float* src, int W, int H, float* level0, float* dst_base,
@@ -355,7 +358,7 @@ hipError_t launch_finite_check(const TileK& T, hipStream_t stream) {
 
 hipError_t launch_maxmip(const float* src, int sw, int sh, float* dst_base, const int* dst_off,
                          const int* dst_w, const int* dst_h, int F, const float* below, int bw,
-                         int bh, int last, unsigned key, hipStream_t stream) {
+                         int bh, int last, unsigned key, bool check, hipStream_t stream) {
   MipDst d;
   d.below = below;
   d.bw = bw;
@@ -372,13 +375,16 @@ hipError_t launch_maxmip(const float* src, int sw, int sh, float* dst_base, cons
   if (nb == 0) return hipSuccess;
   const int vec_ok = ((reinterpret_cast<uintptr_t>(src) & 15) == 0) && (sw % 4 == 0);
   dim3 grid(nb), block(256);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, src, sw, sh, dst_base, d, nbx, vec_ok);
+  };
   switch (F) {
-    case 1: hipLaunchKernelGGL(maxmip_kernel<1>, grid, block, 0, stream, src, sw, sh, dst_base, d, nbx, vec_ok); break;
-    case 2: hipLaunchKernelGGL(maxmip_kernel<2>, grid, block, 0, stream, src, sw, sh, dst_base, d, nbx, vec_ok); break;
-    case 3: hipLaunchKernelGGL(maxmip_kernel<3>, grid, block, 0, stream, src, sw, sh, dst_base, d, nbx, vec_ok); break;
-    case 4: hipLaunchKernelGGL(maxmip_kernel<4>, grid, block, 0, stream, src, sw, sh, dst_base, d, nbx, vec_ok); break;
-    case 5: hipLaunchKernelGGL(maxmip_kernel<5>, grid, block, 0, stream, src, sw, sh, dst_base, d, nbx, vec_ok); break;
-    default: hipLaunchKernelGGL(maxmip_kernel<6>, grid, block, 0, stream, src, sw, sh, dst_base, d, nbx, vec_ok); break;
+    case 1: check ? launch(maxmip_kernel<1, true>) : launch(maxmip_kernel<1, false>); break;
+    case 2: check ? launch(maxmip_kernel<2, true>) : launch(maxmip_kernel<2, false>); break;
+    case 3: check ? launch(maxmip_kernel<3, true>) : launch(maxmip_kernel<3, false>); break;
+    case 4: check ? launch(maxmip_kernel<4, true>) : launch(maxmip_kernel<4, false>); break;
+    case 5: check ? launch(maxmip_kernel<5, true>) : launch(maxmip_kernel<5, false>); break;
+    default: check ? launch(maxmip_kernel<6, true>) : launch(maxmip_kernel<6, false>); break;
   }
   return hipGetLastError();
 }
