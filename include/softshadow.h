@@ -126,7 +126,8 @@ int64_t ss_maxmip_floats(int32_t width, int32_t rows);
  * as +0.  Bit-exact.  fuse_depth = levels written per launch (1..6, 0 = tuned).
  * The float after the top texel (inside the total size) records whether every
  * height is finite: stepping passes over terrain only where that is known, so a
- * mipmap that was not built here is correct to use but slower to step through.
+ * mipmap that was not built here is correct to use but slower to step through (so is
+ * one that a batched call of SS_MODE_DP or SS_MODE_POINT built: it does not look).
  * Per-tile calls in SS_MODE_UNIFORM and SS_MODE_EXACT (prune = 1, nothing
  * recorded) look at the heights again and take that record back if one has gone
  * missing since the build; nothing else in a mipmap changes after it.
@@ -411,6 +412,14 @@ int32_t ss_probe_gather_tiles(const float* d_src, int32_t width, int32_t rows, i
  * FP32 FMAs in eight independent chains; d_out[n_workgroups * 256] receives
  * the lanes' sums.  Rate = 8192 n_workgroups iters / time lane-FMAs per second. */
 int32_t ss_probe_valu(int32_t iters, int64_t n_workgroups, float* d_out, void* stream);
+
+/* Rounding probe (not part of the method): the kernels' short forms of reciprocal,
+ * root and quotient against the general ones, for every mantissa of the exponents
+ * `exponent` and `exponent` + 1 (within +-90; quotients with four numerators each,
+ * FP64 ones with pseudo-random operands).  ADDS the number of results that differ in
+ * any bit to d_counts[5] (8-byte aligned): 1/x, sqrt(x), a/x, and in FP64 n/d and n/d
+ * with 1/d known.  All stay 0. */
+int32_t ss_probe_rounding(int32_t exponent, uint64_t* d_counts, void* stream);
 
 /* Text for a status code (for SS_ERR_HIP: the last HIP error of this thread). */
 const char* ss_status_string(int32_t status);

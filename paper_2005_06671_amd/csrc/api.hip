@@ -659,6 +659,15 @@ extern "C" int32_t ss_probe_valu(int32_t iters, int64_t n_workgroups, float* d_o
   return SS_OK;
 }
 
+extern "C" int32_t ss_probe_rounding(int32_t exponent, uint64_t* d_counts, void* stream) {
+  if (!d_counts || (reinterpret_cast<uintptr_t>(d_counts) & 7) != 0 || exponent < -90 ||
+      exponent > 90)
+    return SS_ERR_INVALID_ARG;
+  SS_HIP(launch_rounding_probe(exponent, reinterpret_cast<unsigned long long*>(d_counts),
+                               (hipStream_t)stream));
+  return SS_OK;
+}
+
 extern "C" int32_t ss_shadow_cast_backward(const ss_tile* tile, const ss_sun* sun,
                                            const ss_params* params, const float* d_grad_shadow,
                                            float* d_grad_height, double* d_grad_sun, void* stream) {

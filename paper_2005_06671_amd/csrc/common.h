@@ -152,21 +152,23 @@ __host__ __device__ inline float run_start_len(int a, double half_delta) {
 #ifdef __HIP_DEVICE_COMPILE__
 #define SS_RCP_SEED(x) __builtin_amdgcn_rcpf(x)
 #define SS_RSQ_SEED(x) __builtin_amdgcn_rsqf(x)
+#define SS_RCP64_SEED(x) __builtin_amdgcn_rcp(x)
 #else  // the host pass only parses the kernels
 #define SS_RCP_SEED(x) (1.0f / (x))
 #define SS_RSQ_SEED(x) (1.0f / sqrtf(x))
+#define SS_RCP64_SEED(x) (1.0 / (x))
 #endif
 
 // The correctly rounded reciprocal, root and quotient, as 1.0f / x, sqrtf(x) and
 // a / b give them, where operands and results are normal numbers with exponents
-// well inside the range: without the scaling and special cases of the general
-// sequences they take 3, 5 and 5 (given y = rcp_rn(b)) instructions in place of
-// 11, 16 and 11.  The hardware's reciprocal and reciprocal root are within an
-// ulp; one Newton step rounds correctly for every mantissa (all 2^24 of two
-// adjacent exponents compared with the general forms on gfx950, at seven places
-// of the range).  The quotient follows from a correctly rounded y by Markstein's
-// theorem: after the first correction q is within an ulp, after the second it is
-// rounded correctly.
+// well inside the range (a numerator below 2^-100 leaves a residual of denormals):
+// without the scaling and special cases of the general sequences they take 3, 5 and
+// 5 (given y = rcp_rn(b)) instructions in place of 11, 16 and 11.  The hardware's
+// reciprocal and reciprocal root are within an ulp; one Newton step rounds correctly
+// for every mantissa (no theorem, but there are only 2^24 of two adjacent exponents:
+// ss_probe_rounding compares them all with the general forms).  The quotient follows
+// from a correctly rounded y by Markstein's theorem: after the first correction q is
+// within an ulp, after the second it is rounded correctly.
 __device__ inline float rcp_rn(float x) {
   const float y = SS_RCP_SEED(x);
   return fmaf(fmaf(-x, y, 1.0f), y, y);
@@ -179,6 +181,24 @@ __device__ inline float div_rn(float a, float b, float y) {
   float q = a * y;
   q = fmaf(fmaf(-b, q, a), y, q);
   return fmaf(fmaf(-b, q, a), y, q);
+}
+
+// n / d in FP64 rounded correctly for operands and results inside the range: the
+// general sequence without its scaling and fix-up, which leave such operands alone.
+__device__ inline double quot64_rn(double n, double d) {
+  double y = SS_RCP64_SEED(d);
+  y = fma(fma(-d, y, 1.0), y, y);
+  y = fma(fma(-d, y, 1.0), y, y);
+  const double q = n * y;
+  return fma(fma(-d, q, n), y, q);
+}
+
+// The same for a divisor whose correctly rounded reciprocal y is known: after the
+// second correction the quotient is rounded correctly (Markstein).
+__device__ inline double quot64_by_rn(double n, double d, double y) {
+  double q = n * y;
+  q = fma(fma(-d, q, n), y, q);
+  return fma(fma(-d, q, n), y, q);
 }
 
 // Ray tile shapes: lanes of one wavefront cover TW x TH texels (TW * TH = 64),

@@ -140,6 +140,7 @@ hipError_t launch_gather_probe(const float* src, long long n_floats, long long w
                                float* out, long long n_threads, hipStream_t stream);
 hipError_t launch_gather_tiles_probe(const float* src, int width, int rows, int iters, float* out,
                                      long long n_threads, hipStream_t stream);
+hipError_t launch_rounding_probe(int exponent, unsigned long long* counts, hipStream_t stream);
 hipError_t launch_valu_probe(int iters, long long n_workgroups, float* out, hipStream_t stream);
 
 }  // namespace ss

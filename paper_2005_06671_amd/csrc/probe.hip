@@ -110,4 +110,49 @@ hipError_t launch_valu_probe(int iters, long long n_workgroups, float* out, hipS
   return hipGetLastError();
 }
 
+// Every mantissa of two adjacent exponents through the short exact forms of common.h and
+// through the general ones, and quotients of which half lie next to the middle of two
+// neighbouring numbers, where a wrong rounding would show first.
+__global__ __launch_bounds__(256) void rounding_probe_kernel(int exponent,
+                                                             unsigned long long* counts) {
+  const unsigned i = blockIdx.x * 256u + threadIdx.x;  // below 2^24
+  const float x = ldexpf(1.0f + (float)(i & 0x7fffffu) * 0x1p-23f, exponent + (int)(i >> 23));
+  auto differ = [](float a, float b) { return __float_as_uint(a) != __float_as_uint(b) ? 1u : 0u; };
+  auto differ64 = [](double a, double b) {
+    return __double_as_longlong(a) != __double_as_longlong(b) ? 1u : 0u;
+  };
+  unsigned r = i * 2654435761u + (unsigned)exponent * 40503u + 97u;
+  auto next = [&] {
+    r ^= r << 13;
+    r ^= r >> 17;
+    r ^= r << 5;
+    return r;
+  };
+  unsigned bad[5] = {0, 0, 0, 0, 0};
+  const float y = rcp_rn(x);
+  bad[0] = differ(y, 1.0f / x);
+  bad[1] = differ(sqrt_rn(x), sqrtf(x));
+  const double d = ldexp(1.0 + (double)next() * 0x1p-32 + (double)(next() >> 12) * 0x1p-52, exponent);
+  const double y64 = 1.0 / d;
+  for (int k = 0; k < 4; ++k) {
+    const int e = max((int)(next() % 61u) - 30, -95 - exponent);  // numerators above 2^-96
+    const float m = ldexpf(1.0f + (float)(next() & 0x7fffffu) * 0x1p-23f, e);
+    const float near = fmaf(x, m, x * ldexpf(1.0f, e - 24));  // x (m + half its last place)
+    const float a = k & 1 ? near : -m;
+    bad[2] += differ(div_rn(a, x, y), a / x);
+    const double m64 = ldexp(1.0 + (double)next() * 0x1p-32 + (double)(next() >> 12) * 0x1p-52, e);
+    const double near64 = fma(d, m64, d * ldexp(1.0, e - 53));
+    const double n = k & 1 ? near64 : -m64;
+    bad[3] += differ64(quot64_rn(n, d), n / d);
+    bad[4] += differ64(quot64_by_rn(n, d, y64), n / d);
+  }
+  for (int k = 0; k < 5; ++k)
+    if (bad[k]) atomicAdd(&counts[k], (unsigned long long)bad[k]);
+}
+
+hipError_t launch_rounding_probe(int exponent, unsigned long long* counts, hipStream_t stream) {
+  hipLaunchKernelGGL(rounding_probe_kernel, dim3(65536), dim3(256), 0, stream, exponent, counts);
+  return hipGetLastError();
+}
+
 }  // namespace ss

@@ -26,24 +26,6 @@ __device__ __forceinline__ double dot3(const double* a, const double* b) {
   return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
 }
 
-// n / d rounded correctly for operands and results inside the range: the general
-// sequence without its scaling and fix-up, which leave such operands alone.
-__device__ __forceinline__ double quotient(double n, double d) {
-  double y = __builtin_amdgcn_rcp(d);
-  y = fma(fma(-d, y, 1.0), y, y);
-  y = fma(fma(-d, y, 1.0), y, y);
-  const double q = n * y;
-  return fma(fma(-d, q, n), y, q);
-}
-
-// The same for a divisor whose correctly rounded reciprocal y is known: after the
-// second correction the quotient is rounded correctly (Markstein).
-__device__ __forceinline__ double quotient_by(double n, double d, double y) {
-  double q = n * y;
-  q = fma(fma(-d, q, n), y, q);
-  return fma(fma(-d, q, n), y, q);
-}
-
 // SAFE: divisions inside the range (the launcher looks at the frames).  A lane
 // takes SS_RES_ROWS texels of one column, whose column part is then formed once.
 // Bound by FP64 instructions, 72 a texel and ten conversions at a quarter of the
@@ -73,11 +55,11 @@ __global__ __launch_bounds__(256) void resample_kernel(ResampleK K) {
     double P[3];
     for (int k = 0; k < 3; ++k) P[k] = C[k] + Y * K.eyd[k];
     const double z = dot3(P, K.cs);
-    const double s = SAFE ? quotient(K.R, z) : K.R / z;
+    const double s = SAFE ? quot64_rn(K.R, z) : K.R / z;
     const double Xs = s * dot3(P, K.exs), Ys = s * dot3(P, K.eys);
     const double ax = Xs - K.oxs, ay = Ys - K.oys;
-    const double qx = (SAFE ? quotient_by(ax, K.Ds, K.invDs) : ax / K.Ds) + 0.5 * (double)K.Ws;
-    const double qy = (SAFE ? quotient_by(ay, K.Ds, K.invDs) : ay / K.Ds) + 0.5 * (double)K.Hs;
+    const double qx = (SAFE ? quot64_by_rn(ax, K.Ds, K.invDs) : ax / K.Ds) + 0.5 * (double)K.Ws;
+    const double qy = (SAFE ? quot64_by_rn(ay, K.Ds, K.invDs) : ay / K.Ds) + 0.5 * (double)K.Hs;
     in[row] = j < K.j1 && z > 0.0 && qx >= 0.0 && qx < (double)K.Ws && qy >= 0.0 && qy < (double)K.Hs;
     const double x = qx - 0.5, y = qy - 0.5;
     const double x0 = floor(x), y0 = floor(y);
