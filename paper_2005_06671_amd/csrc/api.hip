@@ -340,11 +340,10 @@ static int32_t make_tilek(const ss_tile* t, const ss_sun* s, const Resolved& rp,
 // 8192^2, so calls that it cannot pay for step as if a height were missing:
 //   * fewer rays than a 64th of the tile's texels (passing over saves 100 to 400 ps
 //     a ray, the look takes 0.7 ps a texel);
-//   * rays that climb out of the terrain's reach within a few samples.  us with the
-//     look and passing over / without, uniform: 512^2 at 60 deg 25.5 / 31.2, at 85
-//     19.2 / 15.1, 1024^2 at 75 37.8 / 44.8, 256^2 at 45 21.2 / 20.8, at 75 16.5 /
-//     13.2; exact: 1024^2 at 20 deg 190 / 223, at 45 89 / 73, at 75 60 / 50, 512^2 at
-//     20 137 / 140, at 75 29 / 23.
+//   * rays that climb out of the terrain's reach within a few samples: the exact mode's
+//     from SS_EXACT_STEEP on, and uniform steps (us with the look and passing over /
+//     without, 512^2 at 60 deg 25.5 / 31.2, at 85 19.2 / 15.1, 1024^2 at 75 37.8 / 44.8,
+//     256^2 at 45 21.2 / 20.8, at 75 16.5 / 13.2).
 // The exact mode's rays step together to pass over terrain, where its walk lets each go
 // its own way.  That does not pay for a list of points, whose rays may start anywhere
 // (196608 scattered points 357 us together, 210 by the walk; an image's rays start
@@ -360,7 +359,7 @@ static int32_t know_heights(TileK* K, const Resolved& rp, Rays kind, int64_t ray
                             hipStream_t stream) {
   const bool exact = rp.mode == SS_MODE_EXACT;
   if (!steps(rp.mode) || !rp.prune || K->L < 2) return SS_OK;
-  const bool steep = exact ? K->Lz > 0.5f : K->Lz > 0.87f && rays < (1 << 19);
+  const bool steep = exact ? K->Lz > SS_EXACT_STEEP : K->Lz > 0.87f && rays < (1 << 19);
   const bool wide = kind == Rays::tile && (rp.ray_tile == SS_TILE_16x4 || rp.ray_tile == SS_TILE_32x2);
   const bool apart = kind == Rays::list ||
                      (rays <= (1 << 20) && (wide || kind == Rays::adjoint || kind == Rays::image_adjoint));

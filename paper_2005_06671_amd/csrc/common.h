@@ -71,6 +71,11 @@ __device__ __forceinline__ unsigned finite_word(float top, unsigned key) {
   return __builtin_bit_cast(unsigned, top) ^ key;
 }
 
+// The exact mode steps for suns below 30 degrees (the sine) and walks above, where rays
+// climb out of the terrain's reach within a few samples: us stepping / walking, 1024^2
+// at 20 deg 190 / 223, at 45 89 / 73, at 75 60 / 50, 512^2 at 20 137 / 140, at 75 29 / 23.
+#define SS_EXACT_STEEP 0.5f
+
 // Steps are taken SS_CHUNK at a time.
 #define SS_CHUNK 16
 

@@ -1237,7 +1237,7 @@ __device__ __forceinline__ float bound_at(const TileK& T, const int* tab, int m,
 //
 // That walk is for tiles with missing or infinite heights, for prune = 0, for the
 // forward that records the deciding sample (KEEP), for rays that may start anywhere
-// (NEAR false) and where the host has found that it costs less (know_heights).
+// (NEAR false), for steep suns and where the host finds that it costs less (know_heights).
 // Otherwise the wavefront's rays step through the grid together (step_through): 64
 // lanes at levels and samples of their own run every branch of an iteration, so the
 // walk takes as long as its slowest ray at 130 instructions an iteration, mostly
@@ -1269,7 +1269,7 @@ __device__ __forceinline__ RayResult shadow_exact(const TileK& T, const Ray<SPHE
       best = d.key;
     }
   }
-  if (!KEEP && NEAR && T.prune == 1 && heights_finite(T)) {
+  if (!KEEP && NEAR && T.prune == 1 && T.Lz <= SS_EXACT_STEEP && heights_finite(T)) {
     res.key = best;
     step_through(T, r, top, T.half_delta, chunk_level(0.5), true, res, n_smp);
     return res;
