@@ -223,9 +223,13 @@ static int32_t check_sun(const ss_sun* s) {
   return SS_OK;
 }
 
-// Workgroups of 256 lanes one device holds at once (8 per CU at 8 wavefronts
-// per SIMD): the per-tile kernels remap workgroup ids within groups of this
-// many.  Cached per device.
+// Workgroups of 256 lanes one device can hold (8 per CU, at 8 wavefronts per SIMD):
+// the per-tile kernels remap workgroup ids within groups of this many.  Kernels held
+// to 7 or 6 wavefronts keep 1792 or 1536 of 2048 resident, but groups of that size are
+// no better over the range: ms of descents in groups of 1792 / 2048, 4096^2 at 0.2 deg
+// 1.065 / 1.026 and 1.021 / 0.964, at 1.5 deg 0.828 / 0.839, 2048^2 0.246 / 0.254;
+// only 16384^2, whose rows are 1024 workgroups, prefers any size that is no multiple
+// of them (17.8 / 21.6).  Cached per device.
 static int device_wg_group() {
   static std::atomic<int> cache[64];
   int dev = 0;

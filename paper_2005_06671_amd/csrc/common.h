@@ -49,7 +49,7 @@ struct TileK {
   int prune;                 // 1: result-invariant early exits enabled; 2: but stepping passes
                              // over nothing (the heights may not all be finite)
   int wg_group;              // per-tile kernels: workgroup ids are remapped within groups of
-                             // this many (one device-full, a multiple of 8)
+                             // this many (8 per CU: twice the SIMDs)
   int ulev;                  // uniform stepping: chunk_level
   unsigned fit_err[SS_FITRUNS];  // run j: error bounds of the tip height's fits (fit_err_pack)
 };

@@ -1100,7 +1100,7 @@ __device__ __forceinline__ void take_step(const Ray<SPHERE>& r, int k, float t, 
 }
 
 // N steps from step k, for which steps_whole holds: as sample_at without the clamps,
-// two 8-byte gathers a step, four steps' gathers in flight.
+// two 8-byte gathers a step, the N steps' gathers in flight together.
 template <bool SPHERE, int N>
 __device__ __forceinline__ void steps_inside(const TileK& T, const Ray<SPHERE>& r, const Level& L0,
                                              float step, int k, RayResult& res, unsigned& n_smp) {
@@ -1132,11 +1132,12 @@ __device__ __forceinline__ void steps_inside(const TileK& T, const Ray<SPHERE>& 
 // Steps that all count and lie inside the tile run without clamps.
 //
 // Bound by instruction issue (53 a step inside, 65 with the clamps and four gathers;
-// 50 a look at the terrain's maxima) and by the gathers' latency, so half a chunk's
-// gathers are in flight at once.  A 1024^2 tile at 1.5 deg, one-texel steps to 30 km:
-// 764 us step by step, 600 without the clamps, 285 passing over 64 and 16 steps, 262
-// with the halves; eight gathers at a time 245.  A fourth size of 256 steps is worth
-// 2% or costs as much, and sizes that double and halve as they go cost 10% more.
+// 50 a look at the terrain's maxima) and by the gathers' latency, so the gathers of
+// half a chunk, two a step, are in flight at once.  A 1024^2 tile at 1.5 deg, one-texel
+// steps to 30 km: 764 us step by step, 600 without the clamps, 285 passing over 64 and
+// 16 steps, 262 with the halves, 245 with the gathers of eight steps at a time for four.
+// A fourth size of 256 steps is worth 2% or costs as much, and sizes that double and
+// halve as they go cost 10% more.
 template <bool SPHERE>
 __device__ __forceinline__ void step_through(const TileK& T, const Ray<SPHERE>& r, float top,
                                              float step, int lev, bool pass, RayResult& res,
