@@ -130,7 +130,9 @@ int64_t ss_maxmip_floats(int32_t width, int32_t rows);
  * one that a batched call of SS_MODE_DP or SS_MODE_POINT built: it does not look).
  * Per-tile calls in SS_MODE_UNIFORM and SS_MODE_EXACT (prune = 1, nothing
  * recorded) look at the heights again and take that record back if one has gone
- * missing since the build; nothing else in a mipmap changes after it.
+ * missing since the build; nothing else in a mipmap changes after it.  Where a
+ * height is missing, one level holds marks until the build's last launch: work that
+ * overlaps a build in time must neither read nor build the same d_maxmip.
  * width or rows == 0 is an empty no-op. */
 int32_t ss_maxmip_build(const float* d_height, int32_t width, int32_t rows, float* d_maxmip,
                         int32_t fuse_depth, void* stream);
